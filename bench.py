@@ -1398,6 +1398,7 @@ def main():
     # copy form in the kernels' names (template argument 2): 0 plain chunks; 2 token-major chunks
     # through LDS, the library's default for every token-major kernel these figures cover
     kform = 0 if wl.layout == 0 else 2
+    token_major = "false" if wl.layout == 0 else "true"
     # the dominant kernel: the class whose kernel takes longer per step
     dominant_host = bool(host_blocks) and (not stage_blocks or (host_avg or 0.0) >= (stage_avg or 0.0))
     dominant_ms = host_avg if dominant_host else stage_avg
@@ -1420,7 +1421,7 @@ def main():
                 "frac_measured": round(achieved / pr["host_link_peak_gbps"], 4) if pr else None}
     else:
         achieved = 2 * stage_per_launch / (dominant_ms / 1e3) / 1e9
-        trs = pmc_traffic(wl.name, "staging_region_copy<true, %d," % kform)
+        trs = pmc_traffic(wl.name, "staging_region_copy<true, %s," % token_major)
         copied = stage_per_launch / (dominant_ms / 1e3) / 1e9
         roof = {"bound": "hbm", "kernel": "staging_region_copy (HBM gather, beside the host-class kernel)",
                 "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
@@ -1436,7 +1437,7 @@ def main():
     hbm_roof = None
     if stage_only:
         a = 2 * stage_bytes / (stage_only["ms_avg"] / 1e3) / 1e9         # bytes read + written in HBM
-        trs = pmc_traffic(wl.name, "staging_region_copy<true, %d," % kform)
+        trs = pmc_traffic(wl.name, "staging_region_copy<true, %s," % token_major)
         hbm_roof = {"bound": "hbm", "kernel": "staging_region_copy (HBM gather, alone)", "achieved": round(a, 1),
                     "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(a / HBM_PEAK_GBPS, 4),
                     "traffic": round(trs["fetch_bytes"] + trs["write_bytes"]) if trs else None,
@@ -1451,7 +1452,7 @@ def main():
     if store and store.get("staging_alone"):
         sa = store["staging_alone"]
         a = 2 * stage_bytes / (sa["ms_avg"] / 1e3) / 1e9
-        trs = pmc_traffic(wl.name, "staging_region_copy<false, %d," % kform)
+        trs = pmc_traffic(wl.name, "staging_region_copy<false, %s," % token_major)
         store_staging_roof = {"bound": "hbm", "kernel": "staging_region_copy<false,...> (HBM store, alone)",
                               "achieved": round(a, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                               "frac": round(a / HBM_PEAK_GBPS, 4),

@@ -421,6 +421,8 @@ int kv_pool_set_bandwidths(kvp_pool *pool, const uint64_t *bandwidths);
 
 #define KVP_LAUNCH_NT_LOAD   1u  /* non-temporal loads */
 #define KVP_LAUNCH_NT_STORE  2u  /* non-temporal stores */
+/* The flags from here to KVP_LAUNCH_TILE, KVP_LAUNCH_UPLOAD apart, shape the
+ * host class's kernel; the staging class accepts and ignores them. */
 #define KVP_LAUNCH_LDS       4u  /* pool_layout 1: stage each chunk through LDS */
 #define KVP_LAUNCH_SPLIT2    8u  /* pool_layout 0: copy each chunk as two half-chunk units
                                     (probe: 256 x 4-vector tiles instead of 256 x 8) */
@@ -439,11 +441,13 @@ int kv_pool_set_bandwidths(kvp_pool *pool, const uint64_t *bandwidths);
 /* Set the grid (workgroups of 256 threads; 0 = library default) and flags
  * of one (class, op) kernel; flags replace the current ones.  Defaults: host
  * class 12 workgroups (token-major pool: 16, 20 for the store); staging class
- * 2^20, i.e. one unit per workgroup up to that many (the launch caps a grid at
- * the call's unit count), with KVP_LAUNCH_NT_LOAD | KVP_LAUNCH_NT_STORE, plus
- * KVP_LAUNCH_SPLIT2 for pool_layout 0 and KVP_LAUNCH_CHUNK_MAJOR for its
- * retrieve; KVP_LAUNCH_NT_STORE for the host-class store; KVP_LAUNCH_LDS for
- * pool_layout 1 except the host-class store.  With the default host-class
+ * one workgroup per 4 KiB moved, up to 2^23 (the launch caps a grid at the
+ * call's own workgroups), with KVP_LAUNCH_NT_LOAD | KVP_LAUNCH_NT_STORE;
+ * KVP_LAUNCH_NT_STORE for the host-class store; KVP_LAUNCH_LDS for the
+ * host-class retrieve of a pool_layout 1 pool.  With the default host-class
+ * store grid, a store whose staging class takes longer than its host class
+ * uses fewer host workgroups, down to a third (the link's writes slow the HBM
+ * kernel beside them).  With the default host-class
  * retrieve grid, a retrieve enqueued while a host-class store kernel of this
  * pool has not finished takes 48 workgroups: with traffic both ways the
  * link's reads need more in flight (measured on MI355X, a 128K-token
@@ -477,9 +481,9 @@ int kv_pool_set_bandwidths(kvp_pool *pool, const uint64_t *bandwidths);
  * engine pointers plus two 8-byte words per present block -- fits in 384
  * words (3 KiB), that list travels
  * in the kernel arguments and both classes run in ONE launch: workgroups up
- * to each class's grid (capped at its units), the copy form of the host
- * class's flags (of the staging class's when no host-class block is moved),
- * without KVP_LAUNCH_XCD and KVP_LAUNCH_CHUNK_MAJOR.  This saves the
+ * to each class's grid (capped at its units), the host class in the copy form
+ * of its flags without KVP_LAUNCH_XCD, KVP_LAUNCH_CHUNK_MAJOR and
+ * KVP_LAUNCH_TILE, the staging class in its default form.  This saves the
  * work-list upload and the wait between two launches (tens of microseconds
  * on MI355X); for a full 32-layer range it covers up to 160 blocks.
  * KVP_LAUNCH_UPLOAD on either class of the op turns it off (one launch per

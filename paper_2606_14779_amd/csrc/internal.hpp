@@ -360,7 +360,7 @@ void drain_timed(Pool &p, kvp_timing_summary *sum);        // transfer.cpp: wait
 struct CopyItem {          // 16 bytes, one block of work
     uint64_t pool;         // device-visible address of the block in its region
     uint32_t slot;         // engine-cache slot
-    uint32_t reserved;
+    uint32_t region;       // host side only: the region it lies in (0 in a ring slot)
 };
 
 struct CopyArgs {
@@ -379,6 +379,11 @@ struct CopyArgs {
     uint32_t row_vec;          //   D*elem_bytes/16
     uint32_t layout;           // 0 head-major, 1 token-major
     uint32_t tile_items;       // > 0: workgroup-owned tiles of this many items x 1 moved chunk
+    // HBM body (staging regions, copy-engine ring), set by the launch
+    uint32_t unit_vecs;        // 16-byte vectors of a wavefront's unit
+    uint32_t chunk_units;      // units of a chunk
+    uint32_t units;            // units of the launch
+    uint32_t group;            // moved chunks ordered together: chunk group, item, chunk, unit
 };
 
 // A call whose work list is small enough travels in the kernel arguments,
@@ -390,7 +395,7 @@ constexpr uint32_t kInlineWords = 384;   // 3 KiB: [chunks cache pointers][items
 struct SmallCallArgs {
     CopyArgs a;                // geometry; a.items and a.cache unused, a.n_items = all items
     uint32_t n_host;           // items [0, n_host) are host-class, the rest staging-class
-    uint32_t grid_host;        // workgroups taking the host-class items (the rest: staging)
+    uint32_t grid_host;        // workgroups taking the host-class items (from the next multiple of 8 on: staging)
     uint64_t words[kInlineWords];
 };
 // passed by value as the kernel's only argument: it must fit the 4 KiB kernel-argument segment

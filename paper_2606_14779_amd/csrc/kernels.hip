@@ -1,37 +1,21 @@
 // Data-movement kernels of the KV pool, for gfx950 (MI355X).
 //
 // Nothing here is a contraction, so there is no MFMA: every kernel is a bit
-// copy of 16-byte vectors.  One unit of work is one (block, layer, K/V)
-// chunk of C bytes, or half of one (KVP_LAUNCH_SPLIT2, plain chunks only).
-// A 256-thread workgroup (four 64-lane wavefronts) copies a whole unit per
-// step; each lane holds up to UNROLL 16-byte loads in flight before it
-// stores, so a workgroup keeps 256*UNROLL*16 bytes in flight (32 KiB at
-// UNROLL = 8, one LLaMA-shaped chunk).  Loads and stores of a wavefront cover
-// 1 KiB of contiguous memory, which the memory system merges into full
-// 128-byte lines.
+// copy of 16-byte vectors between pool blocks and the engine cache.  There are
+// two bodies, since the host link and HBM want opposite shapes.
 //
-// The grid is persistent: workgroup g takes units g, g+G, g+2G, ...  With K
-// moved chunks per block (2L for all layers, fewer for a layer range), unit
-// u is part u % parts of moved chunk (u / parts) % K of work item
-// u / (K*parts), so neighbouring workgroups read neighbouring pieces of the
-// same pool block (the pool side streams through memory in address order).  There is no data
-// reuse; an optional renumbering that gives each of the 8 XCDs contiguous
-// units (KVP_LAUNCH_XCD) measured no better than the round-robin default, and
-// so did the optional chunk-major order (KVP_LAUNCH_CHUNK_MAJOR), in which the
-// units in flight write neighbouring slots of one per-layer engine buffer.
-// The work list and the engine pointer table are read with scalar loads, and
-// the next unit's entries are fetched while the current unit is copied.
-//
-// Five entry points share the body, so that traces and counters tell them
-// apart: host_region_copy (zero-copy reads or writes of pinned host regions
-// over the host link), staging_region_copy (HBM staging regions),
-// ring_slot_copy (a copy-engine ring slot in HBM, whose host-link leg is a
-// hipMemcpy), file_slot_copy (a file regions' ring slot in pinned host
-// memory, filled or emptied by file reads and writes), and small_call_copy
-// (both region classes of a call whose work list fits in the kernel
-// arguments, in one launch with no upload).
-//
-// Three copy forms:
+// Link body (host regions, file-ring slots): the link needs only its
+// bandwidth-delay product in flight, so a dozen persistent 256-thread
+// workgroups (four 64-lane wavefronts) stream whole units.  One unit is one
+// (block, layer, K/V) chunk of C bytes, or half of one (KVP_LAUNCH_SPLIT2,
+// plain chunks only); each lane holds up to UNROLL 16-byte loads in flight
+// before it stores, so a workgroup keeps 256*UNROLL*16 bytes in flight (32 KiB
+// at UNROLL = 8, one LLaMA-shaped chunk).  Workgroup g takes units g, g+G,
+// g+2G, ...  With K moved chunks per block (2L for all layers, fewer for a
+// layer range), unit u is part u % parts of moved chunk (u / parts) % K of
+// work item u / (K*parts), so neighbouring workgroups read neighbouring pieces
+// of the same pool block.  The next unit's entries are fetched while the
+// current unit is copied.  Three copy forms:
 //   - head-major pool chunks: the chunk is [H][bs][D] on both sides; a plain
 //     contiguous copy (this moves the layer axis from inside the block to
 //     the per-layer engine buffers).
@@ -41,6 +25,19 @@
 //   - token-major pool chunks, LDS-staged: the chunk is read contiguously
 //     into LDS, then written contiguously in the other order, so both global
 //     sides are fully contiguous per workgroup.
+//
+// HBM body (staging regions, copy-engine ring slots): see wave_copy_body.
+//
+// The work list and the engine pointer table are read with scalar loads.
+//
+// Five entry points share the bodies, so that traces and counters tell them
+// apart: host_region_copy (zero-copy reads or writes of pinned host regions
+// over the host link), staging_region_copy (HBM staging regions),
+// ring_slot_copy (a copy-engine ring slot in HBM, whose host-link leg is a
+// hipMemcpy), file_slot_copy (a file regions' ring slot in pinned host
+// memory, filled or emptied by file reads and writes), and small_call_copy
+// (both region classes of a call whose work list fits in the kernel
+// arguments, in one launch with no upload).
 
 #include <hip/hip_runtime.h>
 
@@ -58,6 +55,8 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) v4u gv4u;
 
 constexpr uint32_t kThreads = 256;
+constexpr uint32_t kWave = 64;
+constexpr uint32_t kWaves = kThreads / kWave;
 constexpr uint32_t kXcds = 8;     // MI355X: 8 accelerator complex dies, 32 CUs each
 constexpr uint64_t kMaxLdsChunk = 64 * 1024;
 constexpr uint32_t kTileItems = 8;  // KVP_LAUNCH_TILE: work items per workgroup-owned tile
@@ -339,6 +338,80 @@ __device__ __forceinline__ void class_body(const CopyArgs &a)
         chunk_copy_body<GATHER, FORM, UNROLL, NTL, NTS>(a, (citem_t *)a.items, (cptr_t *)a.cache, g, gridDim.x);
 }
 
+// HBM body: one 16-byte vector per lane, one load and one store, for HBM on
+// both sides.  Bound by HBM bandwidth, and there by how the traffic is spread
+// in time, not by bytes in flight: a contiguous 8 GiB copy on this chip moves
+// 5.5 TB/s (read + written) with four vectors per lane and 16 KiB per
+// workgroup, 5.8 with two and 6.4 with one, whose short-lived wavefronts keep
+// the addresses in flight in a window of 8 MiB instead of 32.
+//
+// A unit is one wavefront's 64 vectors (1 KiB) of a chunk, the last of a chunk
+// shorter; a workgroup is four units.  Units are ordered so that the *written*
+// side runs on: the retrieve by groups of 4 chunks (chunk group, work item,
+// chunk, unit: with work items in slot order it writes up to 64-slot runs of
+// four engine buffers while it reads 4-chunk pieces of each block), the store
+// item by item (it writes whole pool blocks).  Within that order each XCD
+// takes runs of 256 workgroups (1 MiB), so that a page is translated and a
+// DRAM row opened by one die and not by all eight: dealt out one by one, the
+// same order measured 5-15 % less for chunks of 16 KiB and more.  Measured on
+// 8.6 GB in 32 KiB chunks with ascending slots, traffic of the kernel alone:
+// retrieve 6465 GB/s against 5694 for half-chunk units of four vectors per
+// lane in chunk order (5240 for this order without the runs); store 6151
+// against 5407.  Chunks that are no whole number of units (6400 bytes)
+// retrieve at 6122 chunk by chunk and at 5770 in groups of four.
+//
+// Token-major chunks take the same body: a lane's source vector is looked up
+// by its destination index, so stores stay contiguous and loads come in rows
+// of head_dim, which the caches merge into whole lines (rows of 256 bytes:
+// 6267 GB/s retrieved against 5560 staged through LDS, whose barrier puts a
+// chunk's loads and stores in turn; 160 bytes: 5692; 64 bytes: 5682).
+constexpr uint32_t kRunShift = 8;     // workgroups of an XCD's run: 2^8
+constexpr uint32_t kChunkGroup = 4;   // chunks of a retrieve's chunk group
+
+// Workgroup b of n in run order: of every 8 * 2^kRunShift workgroups, those of
+// one XCD (dealt round-robin, b % 8) take a contiguous 2^kRunShift, and of a
+// shorter rest an equal share.  A permutation of [0, n).
+__device__ __host__ inline uint32_t run_order(uint32_t b, uint32_t n)
+{
+    constexpr uint32_t kGroup = kXcds << kRunShift;
+    const uint32_t full = n & ~(kGroup - 1), x = b % kXcds;
+    if (b < full) return (b & ~(kGroup - 1)) + (x << kRunShift) + (b & (kGroup - 1)) / kXcds;
+    const uint32_t share = (n - full) / kXcds, longer = (n - full) % kXcds;
+    return full + x * share + (x < longer ? x : longer) + (b - full) / kXcds;
+}
+
+template <bool GATHER, bool TOKEN_MAJOR, bool NTL, bool NTS>
+__device__ __forceinline__ void wave_copy_body(const CopyArgs &a, citem_t *items, cptr_t *table, uint32_t g, uint32_t G)
+{
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const uint32_t nvec = static_cast<uint32_t>(a.chunk_bytes >> 4);
+    const uint32_t wgs = (a.units + kWaves - 1) / kWaves;
+    for (uint32_t b = g; b < wgs; b += G) {
+        const uint32_t u = run_order(b, wgs) * kWaves + wave;
+        if (u >= a.units) continue;
+        const uint32_t per_group = a.n_items * a.chunk_units * a.group;
+        const uint32_t k0 = u / per_group * a.group;
+        uint32_t r = u - k0 * a.n_items * a.chunk_units;
+        const uint32_t per_item = (a.chunks - k0 < a.group ? a.chunks - k0 : a.group) * a.chunk_units;
+        const uint32_t item = r / per_item;
+        r -= item * per_item;
+        const uint32_t kk = r / a.chunk_units;
+        const uint32_t k = k0 + kk;
+        const uint64_t pool = items[item].pool + static_cast<uint64_t>(a.chunk0 + k) * a.chunk_bytes;
+        const uint64_t cache = table[k] + static_cast<uint64_t>(items[item].slot) * a.chunk_bytes;
+        const v4u *src = reinterpret_cast<const v4u *>(GATHER ? pool : cache);
+        v4u *dst = reinterpret_cast<v4u *>(GATHER ? cache : pool);
+        uint32_t v = (r - kk * a.chunk_units) * a.unit_vecs + lane;
+        for (uint32_t i = 0; i < a.unit_vecs; i += kWave, v += kWave) {   // once, but for chunks of gigabytes
+            const uint32_t d = clamp_index(v, nvec);   // loads are never predicated
+            uint32_t w = d;
+            if constexpr (TOKEN_MAJOR) w = src_of<GATHER>(d, a.heads, a.tokens, a.row_vec);
+            const v4u x = load16<NTL>(src + w);
+            if (v < nvec) store16<NTS>(dst + v, x);
+        }
+    }
+}
+
 // One entry point per kind of source, so that traces and counters tell the
 // zero-copy (host link) kernel, the HBM staging kernel and the kernel that
 // empties / fills a copy-engine ring slot apart.  The body is the same.
@@ -348,16 +421,16 @@ __global__ __launch_bounds__(kThreads) void host_region_copy(CopyArgs a)
     class_body<GATHER, FORM, UNROLL, NTL, NTS>(a);
 }
 
-template <bool GATHER, int FORM, int UNROLL, bool NTL, bool NTS>
+template <bool GATHER, bool TOKEN_MAJOR, bool NTL, bool NTS>
 __global__ __launch_bounds__(kThreads) void staging_region_copy(CopyArgs a)
 {
-    class_body<GATHER, FORM, UNROLL, NTL, NTS>(a);
+    wave_copy_body<GATHER, TOKEN_MAJOR, NTL, NTS>(a, (citem_t *)a.items, (cptr_t *)a.cache, blockIdx.x, gridDim.x);
 }
 
-template <bool GATHER, int FORM, int UNROLL, bool NTL, bool NTS>
+template <bool GATHER, bool TOKEN_MAJOR, bool NTL, bool NTS>
 __global__ __launch_bounds__(kThreads) void ring_slot_copy(CopyArgs a)
 {
-    class_body<GATHER, FORM, UNROLL, NTL, NTS>(a);
+    wave_copy_body<GATHER, TOKEN_MAJOR, NTL, NTS>(a, (citem_t *)a.items, (cptr_t *)a.cache, blockIdx.x, gridDim.x);
 }
 
 template <bool GATHER, int FORM, int UNROLL, bool NTL, bool NTS>
@@ -368,7 +441,8 @@ __global__ __launch_bounds__(kThreads) void file_slot_copy(CopyArgs a)
 
 // Both classes of a small call in one launch, the table and the items read
 // from the kernel arguments (scalar loads, as from the work list).  The
-// class split is uniform per workgroup.
+// class split is uniform per workgroup.  FORM to NTS are the host class's
+// copy form; the staging class takes its own body.
 template <bool GATHER, int FORM, int UNROLL, bool NTL, bool NTS>
 __global__ __launch_bounds__(kThreads) void small_call_copy(SmallCallArgs f)
 {
@@ -380,11 +454,17 @@ __global__ __launch_bounds__(kThreads) void small_call_copy(SmallCallArgs f)
     cptr_t *table = (cptr_t *)words;
     citem_t *items = (citem_t *)(words + static_cast<uint64_t>(f.a.chunks) * sizeof(uint64_t));
     CopyArgs a = f.a;
-    const bool host = blockIdx.x < f.grid_host;
-    a.n_items = host ? f.n_host : f.a.n_items - f.n_host;
-    chunk_copy_body<GATHER, FORM, UNROLL, NTL, NTS>(a, host ? items : items + f.n_host, table,
-                                                    host ? blockIdx.x : blockIdx.x - f.grid_host,
-                                                    host ? f.grid_host : gridDim.x - f.grid_host);
+    // the staging-class workgroups start at a multiple of 8, so that their
+    // numbers tell their XCD; up to 7 workgroups between the classes end at once
+    const uint32_t first = (f.grid_host + kXcds - 1) / kXcds * kXcds;
+    if (blockIdx.x < f.grid_host) {
+        a.n_items = f.n_host;
+        chunk_copy_body<GATHER, FORM, UNROLL, NTL, NTS>(a, items, table, blockIdx.x, f.grid_host);
+    } else if (blockIdx.x >= first) {
+        a.n_items = f.a.n_items - f.n_host;
+        wave_copy_body<GATHER, FORM != kPlain, true, true>(a, items + f.n_host, table, blockIdx.x - first,
+                                                           gridDim.x - first);
+    }
 }
 
 // Contiguous streaming copy over tiles of 256*UNROLL vectors (bandwidth probe).
@@ -470,12 +550,8 @@ static void launch_one(const A &a, dim3 g, size_t lds, hipStream_t s)
         hipLaunchKernelGGL((small_call_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
     else if constexpr (CLS == KVP_CLASS_HOST)
         hipLaunchKernelGGL((host_region_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
-    else if constexpr (CLS == KVP_CLASS_STAGING)
-        hipLaunchKernelGGL((staging_region_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
-    else if constexpr (CLS == kClassFile)
-        hipLaunchKernelGGL((file_slot_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
     else
-        hipLaunchKernelGGL((ring_slot_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
+        hipLaunchKernelGGL((file_slot_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
 }
 
 template <uint32_t CLS, bool GATHER, int FORM, int UNROLL, class A>
@@ -516,10 +592,63 @@ static hipError_t launch_dir(const A &a, uint32_t grid, uint32_t flags, hipStrea
     return launch_unroll<CLS, GATHER, kConvert>(a, grid, flags, 0, s);
 }
 
+// Units of the HBM body and their order for a launch of n items.  Launches of
+// over 2^31 units (terabytes) take more vectors per unit, so that a unit index
+// plus the workgroup stride stays within 32 bits.
+static void wave_units(CopyArgs &a, uint32_t n, bool gather)
+{
+    const uint64_t nvec = a.chunk_bytes >> 4, per_vec = static_cast<uint64_t>(n) * a.chunks;
+    uint64_t vecs = kWave;
+    while (per_vec * ((nvec + vecs - 1) / vecs) > (1ull << 31)) vecs *= 2;
+    a.unit_vecs = static_cast<uint32_t>(vecs);
+    a.chunk_units = static_cast<uint32_t>((nvec + vecs - 1) / vecs);
+    a.units = static_cast<uint32_t>(per_vec * a.chunk_units);
+    a.group = !gather ? a.chunks : a.chunk_bytes % (kWave * 16) ? 1u : a.chunks < kChunkGroup ? a.chunks : kChunkGroup;
+}
+
+// Workgroups of the HBM body: one per four units, at most `grid` of them.
+static uint32_t wave_grid(const CopyArgs &a, uint32_t grid)
+{
+    const uint32_t wgs = a.units / kWaves + (a.units % kWaves != 0);
+    return grid == 0 ? 1u : grid < wgs ? grid : wgs;
+}
+
+template <uint32_t CLS, bool GATHER, bool TOKEN_MAJOR, bool NTL, bool NTS>
+static hipError_t launch_wave_one(const CopyArgs &a, dim3 g, hipStream_t s)
+{
+    if constexpr (CLS == KVP_CLASS_STAGING)
+        hipLaunchKernelGGL((staging_region_copy<GATHER, TOKEN_MAJOR, NTL, NTS>), g, dim3(kThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL((ring_slot_copy<GATHER, TOKEN_MAJOR, NTL, NTS>), g, dim3(kThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+template <uint32_t CLS, bool GATHER, bool TOKEN_MAJOR>
+static hipError_t launch_wave_nt(const CopyArgs &a, dim3 g, uint32_t flags, hipStream_t s)
+{
+    const bool ntl = flags & KVP_LAUNCH_NT_LOAD, nts = flags & KVP_LAUNCH_NT_STORE;
+    if (ntl && nts) return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, true, true>(a, g, s);
+    if (ntl) return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, true, false>(a, g, s);
+    if (nts) return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, false, true>(a, g, s);
+    return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, false, false>(a, g, s);
+}
+
+template <uint32_t CLS>
+static hipError_t launch_wave(CopyArgs a, bool gather, uint32_t grid, uint32_t flags, hipStream_t s)
+{
+    wave_units(a, a.n_items, gather);
+    const dim3 g(wave_grid(a, grid));
+    if (a.layout == 0)
+        return gather ? launch_wave_nt<CLS, true, false>(a, g, flags, s) : launch_wave_nt<CLS, false, false>(a, g, flags, s);
+    return gather ? launch_wave_nt<CLS, true, true>(a, g, flags, s) : launch_wave_nt<CLS, false, true>(a, g, flags, s);
+}
+
 hipError_t launch_chunk_copy(const CopyArgs &args, uint32_t cls, bool gather, uint32_t grid, uint32_t flags,
                              hipStream_t s)
 {
     if (args.n_items == 0) return hipSuccess;
+    if (cls == KVP_CLASS_STAGING) return launch_wave<KVP_CLASS_STAGING>(args, gather, grid, flags, s);
+    if (cls == kClassRing) return launch_wave<kClassRing>(args, gather, grid, flags, s);
     CopyArgs a = args;
     // halves of a plain chunk are independent contiguous copies
     a.parts = (a.layout == 0 && (flags & KVP_LAUNCH_SPLIT2) && a.chunk_bytes % 32 == 0) ? 2u : 1u;
@@ -538,12 +667,7 @@ hipError_t launch_chunk_copy(const CopyArgs &args, uint32_t cls, bool gather, ui
     if (cls == KVP_CLASS_HOST)
         return gather ? launch_dir<KVP_CLASS_HOST, true>(a, grid, flags, s)
                       : launch_dir<KVP_CLASS_HOST, false>(a, grid, flags, s);
-    if (cls == KVP_CLASS_STAGING)
-        return gather ? launch_dir<KVP_CLASS_STAGING, true>(a, grid, flags, s)
-                      : launch_dir<KVP_CLASS_STAGING, false>(a, grid, flags, s);
-    if (cls == kClassFile)
-        return gather ? launch_dir<kClassFile, true>(a, grid, flags, s) : launch_dir<kClassFile, false>(a, grid, flags, s);
-    return gather ? launch_dir<kClassRing, true>(a, grid, flags, s) : launch_dir<kClassRing, false>(a, grid, flags, s);
+    return gather ? launch_dir<kClassFile, true>(a, grid, flags, s) : launch_dir<kClassFile, false>(a, grid, flags, s);
 }
 
 hipError_t launch_small_call(SmallCallArgs &f, bool gather, uint32_t grid_host, uint32_t grid_staging,
@@ -555,13 +679,15 @@ hipError_t launch_small_call(SmallCallArgs &f, bool gather, uint32_t grid_host, 
     a.xcd_remap = 0;
     a.chunk_major = 0;
     a.tile_items = 0;
-    auto cap = [&](uint32_t grid, uint32_t n) {
-        const uint64_t units = static_cast<uint64_t>(n) * a.chunks * a.parts;
-        if (n == 0) return 0u;
-        return grid == 0 ? 1u : static_cast<uint32_t>(grid < units ? grid : units);
-    };
-    f.grid_host = cap(grid_host, f.n_host);
-    const uint32_t grid = f.grid_host + cap(grid_staging, a.n_items - f.n_host);
+    const uint64_t host_units = static_cast<uint64_t>(f.n_host) * a.chunks * a.parts;
+    f.grid_host = static_cast<uint32_t>(grid_host < host_units ? grid_host : host_units);
+    uint32_t grid = f.grid_host;
+    const uint32_t n_staging = a.n_items - f.n_host;
+    if (n_staging) {
+        wave_units(a, n_staging, gather);
+        grid = (grid + kXcds - 1) / kXcds * kXcds + wave_grid(a, grid_staging);
+    }
+    if (f.n_host == 0) flags &= ~KVP_LAUNCH_LDS;   // the staging class stages nothing through LDS
     return gather ? launch_dir<kClassSmall, true>(f, grid, flags, s) : launch_dir<kClassSmall, false>(f, grid, flags, s);
 }
 

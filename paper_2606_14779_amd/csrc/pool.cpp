@@ -364,10 +364,11 @@ uint32_t default_grid(uint32_t cls, uint32_t op, const kvp_kv_spec &spec)
     // ms at 16, 201.7 at 12, 206 at 20, 216 at 24), and its store writes the
     // host side in runs of whole chunks while reading HBM by rows (205.3 ms
     // at 20 or 24, 207.4-208.7 at 16, 211.2 at 12).
-    // Staging class: one unit per workgroup, with no grid-stride loop (the
-    // launch caps the grid at the call's unit count), up to 2^20 workgroups.
+    // Staging class: four units (4 KiB) per workgroup, with no grid-stride loop
+    // (the launch caps the grid at the call's own workgroups) up to 2^23
+    // workgroups, 32 GiB; HIP takes fewer than 2^32 threads per launch.
     if (cls == KVP_CLASS_HOST) return spec.pool_layout == 1 ? (op == KVP_OP_STORE ? 20u : 16u) : 12u;
-    return 1u << 20;
+    return 1u << 23;
 }
 
 uint32_t default_flags(uint32_t cls, uint32_t op, const kvp_kv_spec &spec)
@@ -376,28 +377,15 @@ uint32_t default_flags(uint32_t cls, uint32_t op, const kvp_kv_spec &spec)
     // zero-copy writes to host memory: non-temporal stores measured 0.5 %
     // faster and left the HBM kernel beside them less delayed
     if (cls == KVP_CLASS_HOST && op == KVP_OP_STORE) f |= KVP_LAUNCH_NT_STORE;
-    // token-major pools stage each chunk through LDS (contiguous on both
-    // sides), except the host-class store: there the direct conversion keeps
-    // the host-link side contiguous and measured faster (16 workgroups:
-    // 207.4-208.7 ms against 210.6-211.9 through LDS)
-    if (spec.pool_layout == 1 && !(cls == KVP_CLASS_HOST && op == KVP_OP_STORE)) f |= KVP_LAUNCH_LDS;
-    // Staging class: non-temporal loads and stores, one unit per workgroup
-    // (default_grid); head-major pools in half-chunk units, the retrieve in
-    // chunk-major unit order.  Measured on a 128K-token LLaMA-shaped request
-    // placed on measured weights (8145 staging blocks, 17 GB), HBM traffic of
-    // the kernel alone: gather 5608 GB/s this way, 5526 in block order, 4907
-    // with the XCD renumbering, 5166 in workgroup-owned tiles of 8 blocks;
-    // store 5517 against 5418 in chunk-major order and 5103 for 8192
-    // grid-stride workgroups; token-major through LDS, gather 5519 and store
-    // 5353 against 5112 and 5111 in the earlier forms.  A plain copy on this
-    // GPU peaks in the same form (16 KiB per workgroup, non-temporal both
-    // ways) at 5.7 TB/s of traffic, where reads alone reach 7.2 and writes
-    // alone 5.9.  Beside the host-class kernel of the same request the link
-    // rate is unchanged.
-    if (cls == KVP_CLASS_STAGING) {
-        f |= KVP_LAUNCH_NT_LOAD | KVP_LAUNCH_NT_STORE;
-        if (spec.pool_layout == 0) f |= KVP_LAUNCH_SPLIT2 | (op == KVP_OP_RETRIEVE ? KVP_LAUNCH_CHUNK_MAJOR : 0u);
-    }
+    // the host-class retrieve of a token-major pool stages each chunk through
+    // LDS (contiguous on both sides); the store does not: there the direct
+    // conversion keeps the host-link side contiguous and measured faster (16
+    // workgroups: 207.4-208.7 ms against 210.6-211.9 through LDS)
+    if (spec.pool_layout == 1 && cls == KVP_CLASS_HOST && op == KVP_OP_RETRIEVE) f |= KVP_LAUNCH_LDS;
+    // Staging class: non-temporal loads and stores, worth 2-9 % of a contiguous
+    // copy one vector per lane (6407 GB/s of traffic against 6254 with neither
+    // hint at 256 threads, 6137 against 5805 at 1024)
+    if (cls == KVP_CLASS_STAGING) f |= KVP_LAUNCH_NT_LOAD | KVP_LAUNCH_NT_STORE;
     return f;
 }
 

@@ -39,6 +39,22 @@ constexpr uint64_t kForkMinBytes = 32ull << 20;
 // work, loses with more).
 constexpr uint32_t kDuplexReadGrid = 48;
 
+// Host-class store workgroups beside a staging-class store that takes longer.
+// The link's posted writes fill the write path that the HBM kernel shares, and
+// the more of them wait, the slower it gets, so the host class takes only the
+// workgroups with which it ends in about two thirds of the staging class's
+// time (HBM moves 54 bytes for one over the link), a third of its own choice
+// at least.  4096 Qwen3-shaped blocks on measured weights, 20 of them over the
+// link (27 % of the staging class's time alone), took 2400 us with 12 host
+// workgroups, 2193 with 8, 2166 with 3 to 6, 2177 with 2 and 2700 with 1.  A
+// retrieve's reads don't have this effect (2183-2208 us with 12, 2182 with 6).
+uint32_t throttled_store_grid(uint32_t grid, uint64_t host_bytes, uint64_t staging_bytes)
+{
+    const double share = 54.0 * static_cast<double>(host_bytes) / static_cast<double>(staging_bytes);
+    const uint32_t least = (grid + 2) / 3;
+    return std::min(grid, std::max(least, static_cast<uint32_t>(1.5 * share * grid) + 1));
+}
+
 // The live allocation holding the block at map entry e, or an error.
 const Allocation *resolve(const Pool &p, const kvp_loc &e, uint32_t b, const Allocation *hint)
 {
@@ -60,6 +76,40 @@ const Allocation *resolve(const Pool &p, const kvp_loc &e, uint32_t b, const All
     if ((e.offset - a->base) % p.block_bytes != 0 || a->gen != e.gen)
         fail(KVP_ERR_STALE, "map entry " + std::to_string(b) + ": stale generation or block boundary");
     return a;
+}
+
+// Staging-class work items in the order in which the kernel's written side
+// runs on: a retrieve's by engine slot, a store's region by region (a request's
+// blocks of a region are one range, while a striped map alternates between
+// regions); stable.  Pages and DRAM rows of that side are then met once,
+// whatever the block table's order is, and the other side loses nothing, since
+// a block is itself a contiguous megabyte or so.  HBM traffic of 8192 GPT-OSS
+// shaped blocks retrieved with a permuted table: 5321 GB/s in table order, 5901
+// in slot order; of 4096 Qwen3-shaped blocks stored: 6131 in map order, 6219
+// by region.  A radix sort on 11-bit digits: 2 passes cover 4M slots.
+void order_items(std::vector<CopyItem> &items, bool gather, uint32_t limit)
+{
+    auto key = [gather](const CopyItem &i) { return gather ? i.slot : i.region; };
+    auto less = [&](const CopyItem &x, const CopyItem &y) { return key(x) < key(y); };
+    if (std::is_sorted(items.begin(), items.end(), less)) return;
+    if (items.size() < 64) {
+        std::stable_sort(items.begin(), items.end(), less);
+        return;
+    }
+    constexpr uint32_t kDigit = 11, kMask = (1u << kDigit) - 1;
+    std::vector<CopyItem> other(items.size());
+    for (uint32_t shift = 0; shift < 32 && (limit - 1) >> shift; shift += kDigit) {
+        uint32_t at[kMask + 1] = {};
+        for (const CopyItem &i : items) ++at[key(i) >> shift & kMask];
+        uint32_t sum = 0;
+        for (uint32_t &c : at) {
+            const uint32_t n = c;
+            c = sum;
+            sum += n;
+        }
+        for (const CopyItem &i : items) other[at[key(i) >> shift & kMask]++] = i;
+        items.swap(other);
+    }
 }
 
 constexpr size_t kMaxTimedCalls = 4096;
@@ -305,7 +355,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
                 host_blocks.push_back(HostBlock{e.region, e.offset, static_cast<uint32_t>(slot)});
             else
                 items[cls].push_back(
-                    CopyItem{reinterpret_cast<uint64_t>(r.dev) + e.offset, static_cast<uint32_t>(slot), 0u});
+                    CopyItem{reinterpret_cast<uint64_t>(r.dev) + e.offset, static_cast<uint32_t>(slot), e.region});
         }
     }
     if (!wide_slots.empty()) {
@@ -319,6 +369,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     if (dup)
         fail(KVP_ERR_INVALID, gather ? "destination slot " + std::to_string(dup_slot) + " named twice"
                                      : std::string("two map entries name the same pool block"));
+    order_items(items[KVP_CLASS_STAGING], gather, gather ? num_slots : static_cast<uint32_t>(p.regions.size()));
     const uint64_t width = 2ull * (layer_end - layer_begin) * p.chunk_bytes;   // bytes moved per block
     const uint64_t skip = 2ull * layer_begin * p.chunk_bytes;
     std::vector<LinkRun> runs;
@@ -431,6 +482,9 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             check_hip(q, "hipEventQuery");
         }
     }
+    if (!gather && host && fork_staging && lh.default_grid)
+        lh.grid = throttled_store_grid(lh.grid, items[KVP_CLASS_HOST].size() * width,
+                                       items[KVP_CLASS_STAGING].size() * width);
     if (!noalloc && batches.empty() && file_batches.empty() && !p.timing &&
         !((lh.flags | ls.flags) & KVP_LAUNCH_UPLOAD) &&
         chunks + 2 * n_items <= kInlineWords) {

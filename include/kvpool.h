@@ -242,12 +242,13 @@ int kv_pool_store(kvp_pool *pool, const kvp_loc *map, uint32_t n_blocks,
 
 /*
  * Retrieve (Sec. 4.3, "KV Retrieval"): group the present entries by region
- * type, then read the host regions (zero-copy kernel, on `stream`) and the
- * staging regions (HBM gather kernel, on the pool's internal stream forked
- * from `stream` and joined back into it) in parallel.  A small call (see
- * kv_pool_set_launch) runs both in one launch on `stream`; otherwise a call
- * with under 32 MiB of staging-region bytes runs its HBM kernel on `stream`
- * ahead of the host-region kernel, since forking costs more.  Every chunk
+ * type, then read the host regions (zero-copy) and the staging regions (HBM
+ * gather) in parallel, both by one kernel on `stream`.  A timed call, and one
+ * of a token-major pool whose chunks exceed 20 KiB and whose list is too large
+ * for a small call (kv_pool_set_launch), takes two kernels: the HBM one on the
+ * pool's internal stream, forked from `stream` and joined back into it, or, for
+ * under 32 MiB of staging-region bytes, on `stream` ahead of the host-region
+ * one, since forking costs more.  Every chunk
  * lands in slot dst_block_table[b] of layer l's K or V buffer in the engine
  * layout.
  * Absent entries are skipped and every slot not named by a present entry is
@@ -480,14 +481,14 @@ int kv_pool_set_bandwidths(kvp_pool *pool, const uint64_t *bandwidths);
  * copy-engine ring, is not timed, and its work list -- 2 * (layers moved)
  * engine pointers plus two 8-byte words per present block -- fits in 384
  * words (3 KiB), that list travels
- * in the kernel arguments and both classes run in ONE launch: workgroups up
+ * in the kernel arguments of the one launch of both classes: workgroups up
  * to each class's grid (capped at its units), the host class in the copy form
  * of its flags without KVP_LAUNCH_XCD, KVP_LAUNCH_CHUNK_MAJOR and
  * KVP_LAUNCH_TILE, the staging class in its default form.  This saves the
- * work-list upload and the wait between two launches (tens of microseconds
- * on MI355X); for a full 32-layer range it covers up to 160 blocks.
- * KVP_LAUNCH_UPLOAD on either class of the op turns it off (one launch per
- * class after an upload, as for larger calls).  Results are identical.
+ * work-list upload (about 10 microseconds on MI355X); for a full 32-layer
+ * range it covers up to 160 blocks.
+ * KVP_LAUNCH_UPLOAD on either class of the op turns it off (the list is
+ * uploaded first, as for larger calls).  Results are identical.
  * Errors: INVALID (unknown flags; KVP_LAUNCH_SDMA on the staging class or on
  * a placement-only pool), NOMEM, HIP. */
 int kv_pool_set_launch(kvp_pool *pool, uint32_t cls, uint32_t op, uint32_t grid, uint32_t flags);

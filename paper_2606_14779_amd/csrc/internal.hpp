@@ -245,6 +245,7 @@ struct LaunchCfg {
 
 struct Slot {                    // one work-list buffer of the upload ring
     void *host = nullptr;        // pinned
+    void *host_dev = nullptr;    // its device address
     void *dev = nullptr;
     size_t cap = 0;
     hipEvent_t done = nullptr;   // recorded on the caller stream after the call's kernels
@@ -274,6 +275,7 @@ struct ScratchDevice {
     bool ready = false;
     void *dev = nullptr;
     void *host = nullptr;
+    void *host_dev = nullptr;   // its device address
     hipEvent_t staged = nullptr, free = nullptr;
     bool staged_rec = false, free_rec = false;
 };
@@ -308,7 +310,6 @@ struct Pool {
     hipStream_t s_stage = nullptr;     // the staging-class kernel's stream (host class: caller's);
                                        // with KVP_LAUNCH_SDMA the host-link copies' stream instead
     hipEvent_t fork = nullptr, stage_done = nullptr;
-    hipEvent_t uploaded = nullptr;     // a call's work list is in device memory (s_stage)
     // host link, per direction [op]: the last host-class kernel enqueued; the
     // next one (any stream) waits for it, so calls take the link in turn
     hipEvent_t link_done[2] = {nullptr, nullptr};
@@ -386,20 +387,20 @@ struct CopyArgs {
     uint32_t group;            // moved chunks ordered together: chunk group, item, chunk, unit
 };
 
-// A call whose work list is small enough travels in the kernel arguments,
-// and both classes run in one launch: workgroups [0, grid_host) take the
-// host-class items [0, n_host), the others the staging-class items.  There is
-// then no work-list upload and no second launch to wait for.
+// A call that runs both classes in one launch: workgroups [0, grid_host) take
+// the host-class items [0, n_host), those from the next multiple of 8 on the
+// staging-class items.  A work list that is small enough travels in the kernel
+// arguments, with no upload.
 constexpr uint32_t kInlineWords = 384;   // 3 KiB: [chunks cache pointers][items, two words each]
 
-struct SmallCallArgs {
-    CopyArgs a;                // geometry; a.items and a.cache unused, a.n_items = all items
+struct CallArgs {
+    CopyArgs a;                // geometry; a.n_items = all items; a.items, a.cache null: the list is in words
     uint32_t n_host;           // items [0, n_host) are host-class, the rest staging-class
-    uint32_t grid_host;        // workgroups taking the host-class items (from the next multiple of 8 on: staging)
+    uint32_t grid_host;        // workgroups taking the host-class items
     uint64_t words[kInlineWords];
 };
 // passed by value as the kernel's only argument: it must fit the 4 KiB kernel-argument segment
-static_assert(sizeof(SmallCallArgs) <= 4096, "small-call arguments exceed the kernel-argument segment");
+static_assert(sizeof(CallArgs) <= 4096, "call arguments exceed the kernel-argument segment");
 
 // ---------------------------------------------------------------- copy-engine plan (bounce.cpp)
 
@@ -458,11 +459,13 @@ constexpr uint32_t kClassRing = 2;
 constexpr uint32_t kClassFile = 4;   // a file regions' ring slot (pinned host memory)
 hipError_t launch_chunk_copy(const CopyArgs &a, uint32_t cls, bool gather, uint32_t grid, uint32_t flags,
                              hipStream_t s);
-// One launch of both classes for a call whose table and items are already in
-// f.words (f.a.chunks pointers, then f.a.n_items items); the copy form comes
-// from `flags`, the workgroups of each class from its grid, capped at its units.
-hipError_t launch_small_call(SmallCallArgs &f, bool gather, uint32_t grid_host, uint32_t grid_staging,
-                             uint32_t flags, hipStream_t s);
+// One launch of both classes of a call, of the f.a.n_items items in f.words
+// (f.a.items null: f.a.chunks pointers, then the items) or at f.a.items; the
+// host class's copy form comes from `flags`, the workgroups of each class from
+// its grid, capped at its units.
+hipError_t launch_call(CallArgs &f, bool gather, uint32_t grid_host, uint32_t grid_staging, uint32_t flags,
+                       hipStream_t s);
+hipError_t launch_list_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s);   // bytes: multiple of 16
 hipError_t launch_probe_copy(void *dst, const void *src, uint64_t bytes, uint32_t grid,
                              uint32_t flags, hipStream_t s);
 uint32_t default_grid(uint32_t cls, uint32_t op, const kvp_kv_spec &spec);

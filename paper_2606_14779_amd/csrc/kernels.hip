@@ -35,9 +35,8 @@
 // over the host link), staging_region_copy (HBM staging regions),
 // ring_slot_copy (a copy-engine ring slot in HBM, whose host-link leg is a
 // hipMemcpy), file_slot_copy (a file regions' ring slot in pinned host
-// memory, filled or emptied by file reads and writes), and small_call_copy
-// (both region classes of a call whose work list fits in the kernel
-// arguments, in one launch with no upload).
+// memory, filled or emptied by file reads and writes), and both_regions_copy
+// (both region classes of a call in one launch).
 
 #include <hip/hip_runtime.h>
 
@@ -439,20 +438,24 @@ __global__ __launch_bounds__(kThreads) void file_slot_copy(CopyArgs a)
     class_body<GATHER, FORM, UNROLL, NTL, NTS>(a);
 }
 
-// Both classes of a small call in one launch, the table and the items read
-// from the kernel arguments (scalar loads, as from the work list).  The
-// class split is uniform per workgroup.  FORM to NTS are the host class's
-// copy form; the staging class takes its own body.
+// Both classes of a call in one launch: workgroups [0, grid_host) take the
+// host-class items, the others the staging-class items, so the two run side by
+// side with no second stream and no events between.  FORM to NTS are the host
+// class's copy form; the staging class takes its own body.  The table and the
+// items are read with scalar loads, from the kernel arguments (a small call) or
+// from the uploaded work list.  The class split is uniform per workgroup.
 template <bool GATHER, int FORM, int UNROLL, bool NTL, bool NTS>
-__global__ __launch_bounds__(kThreads) void small_call_copy(SmallCallArgs f)
+__global__ __launch_bounds__(kThreads) void both_regions_copy(CallArgs f)
 {
     // f is the kernel's only explicit argument, so it sits at offset 0 of the
     // kernel-argument segment; the table and the items are addressed there
     // (constant address space, scalar loads), never through a copy of f.
     typedef __attribute__((address_space(4))) const char cchar_t;
-    cchar_t *words = (cchar_t *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(SmallCallArgs, words);
-    cptr_t *table = (cptr_t *)words;
-    citem_t *items = (citem_t *)(words + static_cast<uint64_t>(f.a.chunks) * sizeof(uint64_t));
+    cchar_t *words = (cchar_t *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(CallArgs, words);
+    const bool inlined = f.a.items == nullptr;
+    cptr_t *table = inlined ? (cptr_t *)words : (cptr_t *)f.a.cache;
+    citem_t *items = inlined ? (citem_t *)(words + static_cast<uint64_t>(f.a.chunks) * sizeof(uint64_t))
+                             : (citem_t *)f.a.items;
     CopyArgs a = f.a;
     // the staging-class workgroups start at a multiple of 8, so that their
     // numbers tell their XCD; up to 7 workgroups between the classes end at once
@@ -465,6 +468,17 @@ __global__ __launch_bounds__(kThreads) void small_call_copy(SmallCallArgs f)
         wave_copy_body<GATHER, FORM != kPlain, true, true>(a, items + f.n_host, table, blockIdx.x - first,
                                                            gridDim.x - first);
     }
+}
+
+// A call's work list from its pinned buffer to device memory, one 16-byte
+// vector per lane.  A kernel and not a copy: in line on the caller's stream it
+// takes about 4 us and needs neither the copy's own barriers nor an event from
+// another stream (a stream copy of the same list left the stream idle for 23 us
+// before and 11 us after its 4 us).
+__global__ __launch_bounds__(kThreads) void list_copy(const v4u *__restrict__ src, v4u *__restrict__ dst, uint32_t nvec)
+{
+    const uint32_t v = blockIdx.x * kThreads + threadIdx.x;
+    if (v < nvec) store16<false>(dst + v, load16<false>(src + v));
 }
 
 // Contiguous streaming copy over tiles of 256*UNROLL vectors (bandwidth probe).
@@ -506,10 +520,14 @@ ScratchDevice &scratch_setup(int device)
     check_hip(hipGetSymbolAddress(&dev, HIP_SYMBOL(scratch)), "hipGetSymbolAddress(scratch)");
     if (!dev || (reinterpret_cast<uintptr_t>(dev) & 255))
         fail(KVP_ERR_HIP, "scratch symbol has no 256-byte aligned device address");
-    void *host = nullptr;
+    void *host = nullptr, *host_dev = nullptr;
     if (hipHostMalloc(&host, kScratchBytes, hipHostMallocDefault) != hipSuccess || !host) {
         clear_hip_error();
         fail(KVP_ERR_NOMEM, "pinned staging buffer of the static scratch");
+    }
+    if (const hipError_t r = hipHostGetDevicePointer(&host_dev, host, 0); r != hipSuccess) {
+        (void)hipHostFree(host);
+        check_hip(r, "hipHostGetDevicePointer");
     }
     hipEvent_t ev[2] = {nullptr, nullptr};
     for (auto &e : ev) {
@@ -523,6 +541,7 @@ ScratchDevice &scratch_setup(int device)
     }
     sd.dev = dev;
     sd.host = host;
+    sd.host_dev = host_dev;
     sd.staged = ev[0];
     sd.free = ev[1];
     sd.ready = true;
@@ -538,16 +557,16 @@ ScratchDevice &scratch_device(int device)
 
 // ---------------------------------------------------------------- host-side dispatch
 
-constexpr uint32_t kClassSmall = 3;   // dispatch only: small_call_copy
+constexpr uint32_t kClassBoth = 3;   // dispatch only: both_regions_copy
 
 __device__ __host__ inline const CopyArgs &geometry(const CopyArgs &a) { return a; }
-__device__ __host__ inline const CopyArgs &geometry(const SmallCallArgs &f) { return f.a; }
+__device__ __host__ inline const CopyArgs &geometry(const CallArgs &f) { return f.a; }
 
 template <uint32_t CLS, bool GATHER, int FORM, int UNROLL, bool NTL, bool NTS, class A>
 static void launch_one(const A &a, dim3 g, size_t lds, hipStream_t s)
 {
-    if constexpr (CLS == kClassSmall)
-        hipLaunchKernelGGL((small_call_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
+    if constexpr (CLS == kClassBoth)
+        hipLaunchKernelGGL((both_regions_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
     else if constexpr (CLS == KVP_CLASS_HOST)
         hipLaunchKernelGGL((host_region_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
     else
@@ -670,7 +689,7 @@ hipError_t launch_chunk_copy(const CopyArgs &args, uint32_t cls, bool gather, ui
     return gather ? launch_dir<kClassFile, true>(a, grid, flags, s) : launch_dir<kClassFile, false>(a, grid, flags, s);
 }
 
-hipError_t launch_small_call(SmallCallArgs &f, bool gather, uint32_t grid_host, uint32_t grid_staging,
+hipError_t launch_call(CallArgs &f, bool gather, uint32_t grid_host, uint32_t grid_staging,
                              uint32_t flags, hipStream_t s)
 {
     CopyArgs &a = f.a;
@@ -688,7 +707,16 @@ hipError_t launch_small_call(SmallCallArgs &f, bool gather, uint32_t grid_host, 
         grid = (grid + kXcds - 1) / kXcds * kXcds + wave_grid(a, grid_staging);
     }
     if (f.n_host == 0) flags &= ~KVP_LAUNCH_LDS;   // the staging class stages nothing through LDS
-    return gather ? launch_dir<kClassSmall, true>(f, grid, flags, s) : launch_dir<kClassSmall, false>(f, grid, flags, s);
+    return gather ? launch_dir<kClassBoth, true>(f, grid, flags, s) : launch_dir<kClassBoth, false>(f, grid, flags, s);
+}
+
+hipError_t launch_list_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s)
+{
+    const uint32_t nvec = static_cast<uint32_t>(bytes / 16);
+    if (nvec == 0) return hipSuccess;
+    hipLaunchKernelGGL(list_copy, dim3((nvec + kThreads - 1) / kThreads), dim3(kThreads), 0, s,
+                       static_cast<const v4u *>(src), static_cast<v4u *>(dst), nvec);
+    return hipGetLastError();
 }
 
 hipError_t launch_probe_copy(void *dst, const void *src, uint64_t bytes, uint32_t grid, uint32_t flags,

@@ -5,16 +5,16 @@
 // are the two region classes -- pinned host regions, read by a zero-copy
 // kernel over the host link (or by the copy engines through an HBM ring), and
 // HBM staging regions, read by an HBM gather kernel.  "In parallel" means the
-// staging kernel is forked onto the pool's internal stream while the host
-// kernel runs on the caller's stream, and the two are joined again on the
-// caller's stream, so the caller sees one stream-ordered operation.  The store
-// (Alg. 1, offload) is the same path in the other direction.  The per-call
-// work list (the engine-buffer pointers of the moved chunks, then one 16-byte
-// item per block) travels in the kernel arguments of a single launch when it
-// is small enough; otherwise it is written to a pinned buffer and uploaded
-// with one asynchronous copy.  Those buffers come from a ring guarded by
-// events, so a call only blocks when the ring wraps onto work that is still
-// running.
+// two classes are workgroups of one launch on the caller's stream (or, where
+// each class is timed or a class needs LDS, two kernels, the staging one forked
+// onto the pool's internal stream and joined again), so the caller sees one
+// stream-ordered operation.  The store (Alg. 1, offload) is the same path in
+// the other direction.  The per-call work list (the engine-buffer pointers of
+// the moved chunks, then one 16-byte item per block) travels in the kernel
+// arguments when it is small enough; otherwise it is written to a pinned buffer
+// and uploaded by a small kernel ahead of the call's.  Those buffers come from a
+// ring guarded by events, so a call only blocks when the ring wraps onto work
+// that is still running.
 
 #include <algorithm>
 
@@ -27,10 +27,10 @@ namespace kvp {
 namespace {
 
 constexpr size_t kSlotMin = 64 * 1024;   // smallest work-list buffer
-// Staging-class bytes below which the HBM kernel runs on the caller's stream
-// ahead of the host-class kernel instead of being forked: forking costs about
-// 25 us of host time per call, more than such a kernel takes (32 MiB read and
-// written at ~2.5 TB/s copied: ~13 us).
+// Two kernels for the two classes: staging-class bytes below which the HBM
+// kernel runs on the caller's stream ahead of the host-class kernel instead of
+// being forked.  Forking costs about 25 us of host time per call, more than
+// such a kernel takes (32 MiB read and written at ~2.5 TB/s copied: ~13 us).
 constexpr uint64_t kForkMinBytes = 32ull << 20;
 // Host-class retrieve workgroups while a host-class store of this pool is in
 // flight.  Under two-way traffic the reads need more in flight: a 128K-token
@@ -38,6 +38,7 @@ constexpr uint64_t kForkMinBytes = 32ull << 20;
 // 320 ms with the 12 that a lone retrieve wants (which, beside HBM-bound
 // work, loses with more).
 constexpr uint32_t kDuplexReadGrid = 48;
+constexpr uint64_t kMergeLdsMax = 20 * 1024;   // 160 KiB of LDS hold 8 workgroups of this size
 
 // Host-class store workgroups beside a staging-class store that takes longer.
 // The link's posted writes fill the write path that the HBM kernel shares, and
@@ -149,6 +150,7 @@ Slot &acquire_slot(Pool &p, size_t bytes)
         }
         s.host = h;
         s.dev = d;
+        check_hip(hipHostGetDevicePointer(&s.host_dev, h, 0), "hipHostGetDevicePointer");
         s.cap = cap;
     }
     return s;
@@ -466,11 +468,17 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         }
     };
 
-    // the internal stream takes work only for enough staging bytes or for ring batches
-    const bool fork_staging = batches.empty() && items[KVP_CLASS_STAGING].size() * width >= kForkMinBytes;
     const LaunchCfg &ls = p.launch[KVP_CLASS_STAGING][op];
     LaunchCfg lh = p.launch[KVP_CLASS_HOST][op];
     const bool host = !items[KVP_CLASS_HOST].empty();
+    // One launch for both classes, unless each is timed or the host class's LDS
+    // would hold the HBM kernel's workgroups back (their wavefronts fill a CU
+    // with 8 workgroups).  In two launches the internal stream takes the staging
+    // class, for enough of its bytes.
+    const bool lds = p.spec.pool_layout == 1 && (lh.flags & KVP_LAUNCH_LDS) != 0;
+    const bool one_launch = batches.empty() && (noalloc || !p.timing) && !(lds && p.chunk_bytes > kMergeLdsMax);
+    const bool large = batches.empty() && items[KVP_CLASS_STAGING].size() * width >= kForkMinBytes;
+    const bool fork_staging = large && host && !one_launch;
     if (gather && host && lh.default_grid && p.link_rec[KVP_OP_STORE] && lh.grid < kDuplexReadGrid &&
         hipPeekAtLastError() == hipSuccess) {   // never clear an error the caller has yet to read
         // a store's host-class kernel not yet finished: the link carries traffic both ways
@@ -482,16 +490,14 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             check_hip(q, "hipEventQuery");
         }
     }
-    if (!gather && host && fork_staging && lh.default_grid)
+    if (!gather && host && large && lh.default_grid)
         lh.grid = throttled_store_grid(lh.grid, items[KVP_CLASS_HOST].size() * width,
                                        items[KVP_CLASS_STAGING].size() * width);
     if (!noalloc && batches.empty() && file_batches.empty() && !p.timing &&
         !((lh.flags | ls.flags) & KVP_LAUNCH_UPLOAD) &&
         chunks + 2 * n_items <= kInlineWords) {
-        // Small call: table and items in the kernel arguments, both classes in
-        // one launch in the host class's copy form (the link-bound part; the
-        // form does not change what is written)
-        SmallCallArgs f = {};
+        // Small call: table and items in the kernel arguments
+        CallArgs f = {};
         f.a = geo;
         f.a.n_items = static_cast<uint32_t>(n_items);
         f.n_host = static_cast<uint32_t>(items[KVP_CLASS_HOST].size());
@@ -500,7 +506,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         std::copy(items[0].begin(), items[0].end(), list);
         std::copy(items[1].begin(), items[1].end(), list + items[0].size());
         if (host) take_link();
-        check_hip(launch_small_call(f, gather, lh.grid, ls.grid, host ? lh.flags : ls.flags, s), "kernel launch");
+        check_hip(launch_call(f, gather, lh.grid, ls.grid, lh.flags, s), "kernel launch");
         if (host) hand_back_link();
         mark_requests();
         return;
@@ -531,34 +537,15 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     std::copy(items[1].begin(), items[1].end(), list + items[0].size());
     std::copy(file_items.begin(), file_items.end(), list + items[0].size() + items[1].size());
 
-    // With earlier work still running on the caller's stream (calls issued
-    // back to back, e.g. one per layer), the upload goes on the pool's stream:
-    // it is done while the previous call's host-link kernel still runs, where
-    // in line it would leave the link idle between the two kernels (74 us per
-    // layer call, against 36.5 us).  On an idle caller stream it stays in
-    // line, which costs less host time (9.5 against 26 us per call: the wait
-    // on a pending event from another stream is what costs).  The slot is free
-    // on the device: it was reclaimed only after the last call that read it.
-    bool ahead = false;
-    if (!noalloc && hipPeekAtLastError() == hipSuccess) {   // never clear an error the caller has yet to read
-        const hipError_t q = hipStreamQuery(s);
-        if (q == hipErrorNotReady) {
-            (void)hipGetLastError();   // "not ready" is the answer, not an error to leave behind
-            ahead = true;
-        } else {
-            check_hip(q, "hipStreamQuery");
-        }
-    }
     if (noalloc) {
         // the array is overwritten only after the previous call's kernels
         // (from any pool, on any stream) have read it
         if (sd->free_rec) check_hip(hipStreamWaitEvent(s, sd->free, 0), "hipStreamWaitEvent");
-        check_hip(hipMemcpyAsync(dev_base, host_list, bytes, hipMemcpyHostToDevice, s), "hipMemcpyAsync");
+        check_hip(launch_list_copy(dev_base, sd->host_dev, round_up(bytes, 16), s), "kernel launch");
         check_hip(hipEventRecord(sd->staged, s), "hipEventRecord");
         sd->staged_rec = true;
     } else {
-        check_hip(hipMemcpyAsync(dev_base, host_list, bytes, hipMemcpyHostToDevice, ahead ? p.s_stage : s),
-                  "hipMemcpyAsync");
+        check_hip(launch_list_copy(dev_base, slot->host_dev, round_up(bytes, 16), s), "kernel launch");
         slot->pending = true;  // from here on the slot is in use even if a launch fails
     }
     // After a failure once the work list is on its way (a file read or write
@@ -587,19 +574,15 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         clear_hip_error();
     };
     auto enqueue = [&] {
-        if (ahead) {
-            check_hip(hipEventRecord(p.uploaded, p.s_stage), "hipEventRecord");
-            check_hip(hipStreamWaitEvent(s, p.uploaded, 0), "hipStreamWaitEvent");
-        }
         if (fork_staging || !batches.empty() || !file_batches.empty())
             check_hip(hipEventRecord(p.fork, s), "hipEventRecord");
 
         const CopyItem *dev_list = reinterpret_cast<const CopyItem *>(static_cast<char *>(dev_base) + ptr_bytes);
-        // Staging class forked onto the internal stream first, then the host
-        // class on the caller's stream itself; the caller's stream then waits for
-        // the staging kernel.  One extra stream keeps the pool within the few
-        // hardware queues a process gets, so caller streams (e.g. compute
-        // overlapping a layerwise retrieve) are not serialised behind it.
+        // Two launches: the staging class forked onto the internal stream first,
+        // then the host class on the caller's stream itself; the caller's stream
+        // then waits for the staging kernel.  One extra stream keeps the pool
+        // within the few hardware queues a process gets, so caller streams (e.g.
+        // compute overlapping a layerwise retrieve) are not serialised behind it.
         size_t first = 0;
         CopyArgs args[2] = {geo, geo};
         for (uint32_t c = 0; c < 2; ++c) {
@@ -619,7 +602,15 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             }
         };
         const bool staging = !items[KVP_CLASS_STAGING].empty();
-        if (batches.empty()) {
+        if (one_launch && host && staging) {
+            CallArgs f = {};
+            f.a = args[KVP_CLASS_HOST];
+            f.a.n_items += args[KVP_CLASS_STAGING].n_items;
+            f.n_host = args[KVP_CLASS_HOST].n_items;
+            take_link();
+            check_hip(launch_call(f, gather, lh.grid, ls.grid, lh.flags, s), "kernel launch");
+            hand_back_link();
+        } else if (batches.empty()) {
             if (fork_staging) {
                 check_hip(hipStreamWaitEvent(p.s_stage, p.fork, 0), "hipStreamWaitEvent");
                 launch(KVP_CLASS_STAGING, p.s_stage);

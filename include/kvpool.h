@@ -269,26 +269,27 @@ int kv_pool_retrieve(kvp_pool *pool, const kvp_loc *map, uint32_t n_blocks,
  * call (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc).  Same arguments, semantics, validation, stream ordering
  * and results as kv_pool_retrieve, except:
- *   - The work list (the engine pointers of the moved chunks, 8 bytes each,
- *     rounded up to 16, then 16 bytes per present block) goes through a
- *     static device array of KVP_NOALLOC_SCRATCH_BYTES (1 MiB) that the
- *     library holds once per GPU from the first kv_pool_create on that GPU
- *     until the process ends, with a pinned host buffer of the same size set
- *     up beside it.  A call whose list is larger -- more than 65,504 present
- *     blocks for a 32-layer model -- fails with KVP_ERR_INVALID before any
- *     work is enqueued.
+ *   - A work list too large for a small call (the engine pointers of the moved
+ *     chunks, 8 bytes each, rounded up to 16, then 16 bytes per present block)
+ *     goes through a static device array of KVP_NOALLOC_SCRATCH_BYTES (1 MiB)
+ *     that the library holds once per GPU from the first kv_pool_create on
+ *     that GPU until the process ends, with a pinned host buffer of the same
+ *     size set up beside it.  A call whose list is larger -- more than 65,504
+ *     present blocks for a 32-layer model -- fails with KVP_ERR_INVALID before
+ *     any work is enqueued.
  *   - The call makes no device or pinned allocation (no hipMalloc,
  *     hipHostMalloc, hipFree or other allocating routine) and creates no
  *     stream or event.  The host class always runs the zero-copy kernel
  *     (KVP_LAUNCH_SDMA is ignored: its ring is memory of its own); the call
- *     is never a small-call launch and is not timed.
- *   - The array is shared by every pool and every call on that GPU, and it
- *     keeps the last call's list; nothing in it needs to start at zero.  The
- *     library orders its users: a call's upload waits on the device for the
- *     kernels of the previous such call on that GPU (any pool, any stream),
- *     and the host waits, if need be, until the previous call's upload has
- *     left the pinned buffer.  Calls on one GPU therefore run in the order
- *     they were enqueued rather than overlapping.
+ *     is not timed.
+ *   - The array is shared by every pool and every call on that GPU, which take
+ *     its two halves in turn (a list larger than a half takes both); nothing
+ *     in it needs to start at zero.  The library orders its users: the host
+ *     waits, if need be, until the kernels of the last call that used the half
+ *     (any pool, any stream) are done.  A graph that captured a call reads its
+ *     list from the half when it is replayed, so it is valid until two further
+ *     such calls were made on that GPU (one, for a list larger than a half);
+ *     the list of a small call is part of the graph itself.
  * Errors: as kv_pool_retrieve.
  */
 #define KVP_NOALLOC_SCRATCH_BYTES (1u << 20)

@@ -132,12 +132,9 @@ struct RequestRec {
     uint32_t n_blocks;              // over all offload sets (place, then each extend)
     uint32_t gen;
     std::deque<Allocation> ranges;  // one per (offload set, region); stable addresses
-    hipEvent_t stored = nullptr;   // recorded after each store touching the request
-    hipEvent_t busy = nullptr;     // recorded after each store / retrieve touching it; each record
-                                   // covers the one before it, so it waits for every earlier call
-    bool stored_rec = false;
-    bool busy_rec = false;
-    hipStream_t busy_stream = nullptr;   // stream of the last busy record
+    uint64_t stored_call = 0;       // the last store touching the request (see flight.cpp; 0: none)
+    uint64_t busy_call = 0;         // the last store / retrieve touching it; each covers the one
+                                    // before it, so its completion is that of every earlier call
     uint64_t call_mark = 0;         // the last store / retrieve call that listed it (pool lock held)
 };
 
@@ -248,8 +245,12 @@ struct Slot {                    // one work-list buffer of the upload ring
     void *host_dev = nullptr;    // its device address
     void *dev = nullptr;
     size_t cap = 0;
-    hipEvent_t done = nullptr;   // recorded on the caller stream after the call's kernels
-    bool pending = false;
+    uint64_t call = 0;           // the last call that used it (0: none)
+};
+
+struct FlightRec {               // one store / retrieve whose completion was not seen yet
+    hipEvent_t done;             // recorded on the caller's stream after all of it
+    hipStream_t stream;
 };
 
 struct TimedCall {                // one store / retrieve recorded while timing is on
@@ -263,9 +264,10 @@ struct TimedCall {                // one store / retrieve recorded while timing 
 // GPU (kernels.hip), shared by every pool and call on that GPU.  `dev` is the
 // array's device address on that GPU (never the array's host-side name);
 // `host` is a pinned buffer of the same size, allocated once with it, in
-// which the host writes a call's list before the upload.  `staged` is
-// recorded after a call's upload (the host buffer may then be rewritten),
-// `free` after its kernels (the device array may then be overwritten).
+// which the host writes a call's list before the upload.  Calls take the two
+// halves in turn (a list larger than a half takes both), so that one call's
+// list is written while the previous call still reads its own; `free[h]` is
+// recorded after the kernels of the last call that used half h.
 // Nothing here is ever released: each GPU keeps them until the process ends,
 // and no destructor makes a HIP call at exit.
 constexpr uint64_t kScratchBytes = 1ull << 20;
@@ -276,8 +278,9 @@ struct ScratchDevice {
     void *dev = nullptr;
     void *host = nullptr;
     void *host_dev = nullptr;   // its device address
-    hipEvent_t staged = nullptr, free = nullptr;
-    bool staged_rec = false, free_rec = false;
+    hipEvent_t free[2] = {nullptr, nullptr};
+    bool free_rec[2] = {false, false};
+    uint32_t next = 0;          // half of the next call
 };
 
 // Set up the scratch of `device` (the current device) on first use: the
@@ -310,11 +313,13 @@ struct Pool {
     hipStream_t s_stage = nullptr;     // the staging-class kernel's stream (host class: caller's);
                                        // with KVP_LAUNCH_SDMA the host-link copies' stream instead
     hipEvent_t fork = nullptr, stage_done = nullptr;
-    // host link, per direction [op]: the last host-class kernel enqueued; the
+    // calls in flight, oldest first (flight.cpp); flight_first is the oldest's number
+    std::deque<FlightRec> flight;
+    uint64_t flight_first = 1;
+    std::vector<hipEvent_t> idle;       // events for later calls
+    // host link, per direction [op]: the last call with a host-class kernel; the
     // next one (any stream) waits for it, so calls take the link in turn
-    hipEvent_t link_done[2] = {nullptr, nullptr};
-    bool link_rec[2] = {false, false};
-    hipStream_t link_stream[2] = {nullptr, nullptr};   // stream of that kernel (same stream: no wait)
+    uint64_t link_call[2] = {0, 0};
     std::vector<Slot> ring;
     uint32_t ring_next = 0;
     LaunchCfg launch[2][2];      // [class][op]
@@ -348,6 +353,14 @@ struct Pool {
 
 // ---------------------------------------------------------------- helpers shared by the pool sources
 
+const FlightRec *in_flight(const Pool &p, uint64_t call);   // flight.cpp: null once it is known to be done
+void wait_call(const Pool &p, uint64_t call);               // host wait
+void land_done_calls(Pool &p);                              // notice finished calls (never under capture)
+// Number the call whose work was just enqueued on s.  Creates no event unless
+// may_create; may wait for the oldest call in flight.
+uint64_t record_call(Pool &p, hipStream_t s, bool may_create);
+void add_idle_event(Pool &p);
+void drain_calls(Pool &p) noexcept;                         // wait for every call, destroy the events
 void free_slot(Slot &s);                                    // pool.cpp: one work-list buffer
 void release_bounce(Pool &p);                               // pool.cpp: copy-engine ring, after its work
 void ensure_bounce(Pool &p);                                // pool.cpp: copy-engine ring on first use

@@ -542,8 +542,8 @@ ScratchDevice &scratch_setup(int device)
     sd.dev = dev;
     sd.host = host;
     sd.host_dev = host_dev;
-    sd.staged = ev[0];
-    sd.free = ev[1];
+    sd.free[0] = ev[0];
+    sd.free[1] = ev[1];
     sd.ready = true;
     return sd;
 }

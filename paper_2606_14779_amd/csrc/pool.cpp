@@ -37,6 +37,7 @@ void check_hip(hipError_t e, const char *what)
 namespace {
 
 constexpr uint32_t kRingSlots = 32;
+constexpr uint32_t kFirstEvents = 32;   // completion events made with the pool (the allocation-free call makes none)
 constexpr uint64_t kCreateProbeBytes = 256ull << 20;   // per-region read probe when no bandwidths are given
 
 // Bind the calling thread's memory policy to one NUMA node for the scope.
@@ -294,20 +295,9 @@ void release_gpu(Pool &p)
     p.workers.reset();   // joins the file regions' worker threads
     for (auto &r : p.regions) close_file_region(r);
     if (p.s_stage) (void)hipStreamSynchronize(p.s_stage);
-    for (auto &s : p.ring) {
-        if (s.pending && s.done) (void)hipEventSynchronize(s.done);
-        free_slot(s);
-        if (s.done) (void)hipEventDestroy(s.done);
-        s.done = nullptr;
-    }
-    for (int op = 0; op < 2; ++op)   // the last host-class kernel of each direction
-        if (p.link_rec[op] && p.link_done[op]) (void)hipEventSynchronize(p.link_done[op]);
-    for (auto &kv : p.requests) {
-        if (kv.second->busy_rec) (void)hipEventSynchronize(kv.second->busy);
-        if (kv.second->stored) (void)hipEventDestroy(kv.second->stored);
-        if (kv.second->busy) (void)hipEventDestroy(kv.second->busy);
-    }
-    hipEvent_t *evs[] = {&p.fork, &p.stage_done, &p.link_done[0], &p.link_done[1]};
+    drain_calls(p);
+    for (auto &s : p.ring) free_slot(s);
+    hipEvent_t *evs[] = {&p.fork, &p.stage_done};
     for (auto e : evs)
         if (*e) (void)hipEventDestroy(*e), *e = nullptr;
     for (auto &tc : p.timed)
@@ -466,9 +456,8 @@ Pool *pool_create(const kvp_region_desc *regions, const uint64_t *bandwidths, ui
         check_hip(hipStreamCreateWithFlags(&p->s_stage, hipStreamNonBlocking), "hipStreamCreate");
         check_hip(hipEventCreateWithFlags(&p->fork, hipEventDisableTiming), "hipEventCreate");
         check_hip(hipEventCreateWithFlags(&p->stage_done, hipEventDisableTiming), "hipEventCreate");
-        for (auto &e : p->link_done) check_hip(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
         p->ring.resize(kRingSlots);
-        for (auto &s : p->ring) check_hip(hipEventCreateWithFlags(&s.done, hipEventDisableTiming), "hipEventCreate");
+        for (uint32_t i = 0; i < kFirstEvents; ++i) add_idle_event(*p);
         (void)scratch_setup(hip_device);   // once per device: the static work-list scratch
         if (!bandwidths) {
             // Eq. 1 from measured bandwidths: each region's read rate into HBM
@@ -572,30 +561,14 @@ void pool_place(Pool &p, uint64_t request, uint32_t n_blocks, kvp_loc *out)
     const SetPlan plan = reserve_set(p, n_blocks);
 
     auto rec = std::make_unique<RequestRec>();
-    if (!p.placement_only) {
-        DeviceScope dev(p.device);
-        check_hip(hipEventCreateWithFlags(&rec->stored, hipEventDisableTiming), "hipEventCreate");
-        hipError_t e = hipEventCreateWithFlags(&rec->busy, hipEventDisableTiming);
-        if (e != hipSuccess) {
-            (void)hipEventDestroy(rec->stored);
-            check_hip(e, "hipEventCreate");
-        }
-    }
     rec->id = request;
     rec->gen = p.next_gen;
     RequestRec *r = rec.get();
-    const hipEvent_t stored = rec->stored, busy = rec->busy;   // the record may be gone in the handler
+    auto slot = p.requests.emplace(request, std::move(rec)).first;
     try {
-        auto slot = p.requests.emplace(request, std::move(rec)).first;
-        try {
-            commit_set(p, *r, plan, 0, n_blocks, out);
-        } catch (...) {
-            p.requests.erase(slot);
-            throw;
-        }
+        commit_set(p, *r, plan, 0, n_blocks, out);
     } catch (...) {
-        if (stored) (void)hipEventDestroy(stored);
-        if (busy) (void)hipEventDestroy(busy);
+        p.requests.erase(slot);
         throw;
     }
     ++p.next_gen;
@@ -659,9 +632,7 @@ void pool_release(Pool &p, uint64_t request)
         if (gives[i]) p.regions[i].alloc.reserve_gives(gives[i]);
     if (!p.placement_only) {
         DeviceScope dev(p.device);
-        if (rec.busy_rec) check_hip(hipEventSynchronize(rec.busy), "hipEventSynchronize");
-        (void)hipEventDestroy(rec.stored);
-        (void)hipEventDestroy(rec.busy);
+        wait_call(p, rec.busy_call);
     }
     for (auto &a : rec.ranges) {
         p.regions[a.region].live.erase(a.base);

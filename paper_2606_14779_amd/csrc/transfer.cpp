@@ -127,14 +127,23 @@ hipEvent_t timing_event(Pool &p)
     return e;
 }
 
+bool stream_capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const bool clean = hipPeekAtLastError() == hipSuccess;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        if (clean) clear_hip_error();   // never an error the caller has yet to read
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 Slot &acquire_slot(Pool &p, size_t bytes)
 {
     Slot &s = p.ring[p.ring_next];
     p.ring_next = (p.ring_next + 1) % static_cast<uint32_t>(p.ring.size());
-    if (s.pending) {
-        check_hip(hipEventSynchronize(s.done), "hipEventSynchronize");
-        s.pending = false;
-    }
+    wait_call(p, s.call);
+    s.call = 0;
     if (s.cap < bytes) {
         free_slot(s);
         const size_t cap = round_up(std::max(bytes, kSlotMin), kSlotMin);
@@ -253,11 +262,11 @@ void drain_timed(Pool &p, kvp_timing_summary *sum)
     if (sum) *sum = s;
 }
 
-// noalloc (retrieve only): the work list goes through the device's static
-// scratch instead of the upload ring, and the host class always takes the
-// zero-copy kernel (the copy-engine ring is memory of its own); no small-call
-// launch and no timing, so that the call makes no allocation and creates no
-// HIP object.
+// noalloc (retrieve only): a work list too large for the kernel arguments goes
+// through the device's static scratch instead of the upload ring, and the host
+// class always takes the zero-copy kernel (the copy-engine ring is memory of
+// its own); no timing, so that the call makes no allocation and creates no HIP
+// object.
 void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t *table, uint32_t num_slots,
                    uint32_t layer_begin, uint32_t layer_end, void *const *k_layers, void *const *v_layers,
                    void *stream_ptr, bool gather, bool noalloc)
@@ -414,41 +423,40 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     if (n_items == 0) return;
 
     hipStream_t s = static_cast<hipStream_t>(stream_ptr);
+    // A call may be captured into a graph if its work list travels in the kernel
+    // arguments or goes through the static scratch; its replays are the caller's
+    // to order, so nothing is recorded for it.
+    const bool capturing = stream_capturing(s);
+    if (!capturing) land_done_calls(p);
+    uint64_t waited = 0;
+    auto wait_for = [&](uint64_t call) {   // in stream order, so only for a call on another stream
+        const FlightRec *f = call == waited ? nullptr : in_flight(p, call);
+        waited = call;
+        if (f && f->stream != s) check_hip(hipStreamWaitEvent(s, f->done, 0), "hipStreamWaitEvent");
+    };
     // ordering with earlier work on the same requests from any stream:
     // retrieve after store (read after write), store after store/retrieve
-    for (RequestRec *rec : touched) {
-        if (gather && rec->stored_rec) check_hip(hipStreamWaitEvent(s, rec->stored, 0), "hipStreamWaitEvent");
-        if (!gather && rec->busy_rec) check_hip(hipStreamWaitEvent(s, rec->busy, 0), "hipStreamWaitEvent");
-    }
-    // busy must cover every call still touching the request, not only this
-    // one: two retrieves of a request may run on different streams at once,
-    // and release, destroy and a later store wait on busy alone.  So when
-    // the previous record was on another stream, the caller's stream first
-    // waits for it (after this call's kernels, so only later work on the
-    // stream is held back), and the new record covers both.
-    auto mark_requests = [&] {
-        for (RequestRec *rec : touched) {
-            if (rec->busy_rec && rec->busy_stream != s)
-                check_hip(hipStreamWaitEvent(s, rec->busy, 0), "hipStreamWaitEvent");
-            check_hip(hipEventRecord(rec->busy, s), "hipEventRecord");
-            rec->busy_rec = true;
-            rec->busy_stream = s;
-            if (!gather) {
-                check_hip(hipEventRecord(rec->stored, s), "hipEventRecord");
-                rec->stored_rec = true;
-            }
-        }
-    };
+    for (RequestRec *rec : touched) wait_for(gather ? rec->stored_call : rec->busy_call);
     // one host-class kernel on the link at a time, in enqueue order: two of
     // them would only share its bandwidth and both end late
-    auto take_link = [&] {
-        if (p.link_rec[op] && p.link_stream[op] != s)
-            check_hip(hipStreamWaitEvent(s, p.link_done[op], 0), "hipStreamWaitEvent");
-    };
-    auto hand_back_link = [&] {
-        check_hip(hipEventRecord(p.link_done[op], s), "hipEventRecord");
-        p.link_rec[op] = true;
-        p.link_stream[op] = s;
+    auto take_link = [&] { wait_for(p.link_call[op]); };
+    // The call's completion.  busy must cover every call still touching the
+    // request, not only this one: two retrieves of a request may run on
+    // different streams at once, and release, destroy and a later store wait on
+    // busy alone.  So when the previous one was on another stream, the caller's
+    // stream first waits for it (after this call's kernels, so only later work
+    // on the stream is held back), and the new one covers both.
+    Slot *slot = nullptr;   // the call's work-list buffer, once it is in use
+    auto finish = [&](bool on_link) {
+        if (capturing) return;
+        for (RequestRec *rec : touched) wait_for(rec->busy_call);
+        const uint64_t call = record_call(p, s, !noalloc);
+        if (slot) slot->call = call;
+        if (on_link) p.link_call[op] = call;
+        for (RequestRec *rec : touched) {
+            rec->busy_call = call;
+            if (!gather) rec->stored_call = call;
+        }
     };
 
     const uint32_t chunks = 2 * (layer_end - layer_begin);
@@ -479,10 +487,11 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     const bool one_launch = batches.empty() && (noalloc || !p.timing) && !(lds && p.chunk_bytes > kMergeLdsMax);
     const bool large = batches.empty() && items[KVP_CLASS_STAGING].size() * width >= kForkMinBytes;
     const bool fork_staging = large && host && !one_launch;
-    if (gather && host && lh.default_grid && p.link_rec[KVP_OP_STORE] && lh.grid < kDuplexReadGrid &&
+    const FlightRec *storing = in_flight(p, p.link_call[KVP_OP_STORE]);
+    if (gather && host && lh.default_grid && storing && lh.grid < kDuplexReadGrid && !capturing &&
         hipPeekAtLastError() == hipSuccess) {   // never clear an error the caller has yet to read
         // a store's host-class kernel not yet finished: the link carries traffic both ways
-        const hipError_t q = hipEventQuery(p.link_done[KVP_OP_STORE]);
+        const hipError_t q = hipEventQuery(storing->done);
         if (q == hipErrorNotReady) {
             (void)hipGetLastError();   // "not ready" is the answer, not an error to leave behind
             lh.grid = kDuplexReadGrid;
@@ -493,7 +502,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     if (!gather && host && large && lh.default_grid)
         lh.grid = throttled_store_grid(lh.grid, items[KVP_CLASS_HOST].size() * width,
                                        items[KVP_CLASS_STAGING].size() * width);
-    if (!noalloc && batches.empty() && file_batches.empty() && !p.timing &&
+    if (batches.empty() && file_batches.empty() && (noalloc || !p.timing) &&
         !((lh.flags | ls.flags) & KVP_LAUNCH_UPLOAD) &&
         chunks + 2 * n_items <= kInlineWords) {
         // Small call: table and items in the kernel arguments
@@ -507,29 +516,37 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         std::copy(items[1].begin(), items[1].end(), list + items[0].size());
         if (host) take_link();
         check_hip(launch_call(f, gather, lh.grid, ls.grid, lh.flags, s), "kernel launch");
-        if (host) hand_back_link();
-        mark_requests();
+        finish(host);
         return;
     }
 
     // work list: [chunks cache pointers][host items][staging items][file items], in a
     // ring slot of the pool, or in the device's static scratch (noalloc)
     const size_t bytes = list_bytes;
-    Slot *slot = nullptr;
+    if (capturing && !noalloc)   // a replay would read a buffer that later calls rewrite
+        fail(KVP_ERR_HIP, "a call with an uploaded work list: operation not permitted when stream is capturing");
     ScratchDevice *sd = nullptr;
+    const bool whole = bytes > kScratchBytes / 2;   // of the scratch
+    uint32_t half = 0;
     std::unique_lock<std::mutex> scratch_lock;
-    void *host_list = nullptr, *dev_base = nullptr;
+    Slot *buffer = nullptr;
+    void *host_list = nullptr, *host_list_dev = nullptr, *dev_base = nullptr;
     if (noalloc) {
         sd = &scratch_device(p.device);   // set up when the pool was created
         scratch_lock = std::unique_lock<std::mutex>(sd->mu);
-        // the pinned buffer is rewritten only after the previous upload from it
-        if (sd->staged_rec) check_hip(hipEventSynchronize(sd->staged), "hipEventSynchronize");
-        host_list = sd->host;
-        dev_base = sd->dev;
+        // a half is rewritten, in either memory, only after the kernels of the
+        // last call that used it (from any pool, on any stream)
+        half = whole ? 0 : sd->next;
+        for (uint32_t h = 0; h < 2; ++h)
+            if ((whole || h == half) && sd->free_rec[h]) check_hip(hipEventSynchronize(sd->free[h]), "hipEventSynchronize");
+        host_list = static_cast<char *>(sd->host) + half * (kScratchBytes / 2);
+        host_list_dev = static_cast<char *>(sd->host_dev) + half * (kScratchBytes / 2);
+        dev_base = static_cast<char *>(sd->dev) + half * (kScratchBytes / 2);
     } else {
-        slot = &acquire_slot(p, bytes);
-        host_list = slot->host;
-        dev_base = slot->dev;
+        buffer = &acquire_slot(p, bytes);
+        host_list = buffer->host;
+        host_list_dev = buffer->host_dev;
+        dev_base = buffer->dev;
     }
     fill_table(static_cast<uint64_t *>(host_list));
     auto *list = reinterpret_cast<CopyItem *>(static_cast<char *>(host_list) + ptr_bytes);
@@ -537,39 +554,32 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     std::copy(items[1].begin(), items[1].end(), list + items[0].size());
     std::copy(file_items.begin(), file_items.end(), list + items[0].size() + items[1].size());
 
-    if (noalloc) {
-        // the array is overwritten only after the previous call's kernels
-        // (from any pool, on any stream) have read it
-        if (sd->free_rec) check_hip(hipStreamWaitEvent(s, sd->free, 0), "hipStreamWaitEvent");
-        check_hip(launch_list_copy(dev_base, sd->host_dev, round_up(bytes, 16), s), "kernel launch");
-        check_hip(hipEventRecord(sd->staged, s), "hipEventRecord");
-        sd->staged_rec = true;
-    } else {
-        check_hip(launch_list_copy(dev_base, slot->host_dev, round_up(bytes, 16), s), "kernel launch");
-        slot->pending = true;  // from here on the slot is in use even if a launch fails
-    }
+    check_hip(launch_list_copy(dev_base, host_list_dev, bytes, s), "kernel launch");
+    slot = buffer;   // from here on the buffer is in use even if a launch fails
+    auto free_scratch = [&] {   // after the call's kernels
+        if (!noalloc || capturing) return;
+        for (uint32_t h = 0; h < 2; ++h) {
+            if (!whole && h != half) continue;
+            check_hip(hipEventRecord(sd->free[h], s), "hipEventRecord");
+            sd->free_rec[h] = true;
+        }
+        sd->next = half ^ 1u;
+    };
     // After a failure once the work list is on its way (a file read or write
     // that fails, a launch or copy the runtime refuses), whatever was enqueued
     // still runs and reads the work list.  So the caller's stream joins the
-    // pool's stream, and the work list's and the requests' completion events
-    // are recorded after all of it before the error is returned: a later call
-    // cannot rewrite the list under those kernels, and release waits for them.
-    // Nothing here throws, so the first error is the one reported.
+    // pool's stream, and the call's completion is recorded after all of it
+    // before the error is returned: a later call cannot rewrite the list under
+    // those kernels, and release waits for them.  Nothing here throws, so the
+    // first error is the one reported.
     auto settle = [&]() noexcept {
         (void)hipEventRecord(p.stage_done, p.s_stage);
         (void)hipStreamWaitEvent(s, p.stage_done, 0);
-        if (noalloc) {
-            if (hipEventRecord(sd->free, s) == hipSuccess) sd->free_rec = true;
-        } else {
-            (void)hipEventRecord(slot->done, s);
-        }
-        for (RequestRec *rec : touched) {
-            if (rec->busy_rec && rec->busy_stream != s) (void)hipStreamWaitEvent(s, rec->busy, 0);
-            if (hipEventRecord(rec->busy, s) == hipSuccess) {
-                rec->busy_rec = true;
-                rec->busy_stream = s;
-            }
-            if (!gather && hipEventRecord(rec->stored, s) == hipSuccess) rec->stored_rec = true;
+        try {
+            free_scratch();
+            finish(host);
+        } catch (...) {
+            (void)hipStreamSynchronize(s);   // nothing was recorded to wait for
         }
         clear_hip_error();
     };
@@ -609,7 +619,6 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             f.n_host = args[KVP_CLASS_HOST].n_items;
             take_link();
             check_hip(launch_call(f, gather, lh.grid, ls.grid, lh.flags, s), "kernel launch");
-            hand_back_link();
         } else if (batches.empty()) {
             if (fork_staging) {
                 check_hip(hipStreamWaitEvent(p.s_stage, p.fork, 0), "hipStreamWaitEvent");
@@ -621,7 +630,6 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             if (host) {
                 take_link();
                 launch(KVP_CLASS_HOST, s);
-                hand_back_link();
             }
             if (fork_staging) check_hip(hipStreamWaitEvent(s, p.stage_done, 0), "hipStreamWaitEvent");
         } else {
@@ -710,13 +718,8 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         settle();
         throw;
     }
-    if (noalloc) {
-        check_hip(hipEventRecord(sd->free, s), "hipEventRecord");
-        sd->free_rec = true;
-    } else {
-        check_hip(hipEventRecord(slot->done, s), "hipEventRecord");
-    }
-    mark_requests();
+    free_scratch();
+    finish(host && batches.empty());
 }
 
 }  // namespace kvp

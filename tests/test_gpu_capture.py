@@ -1,0 +1,121 @@
+"""Calls captured into a HIP graph: those whose work list travels in the kernel arguments, and the
+allocation-free retrieve through the static scratch.  Every replay is checked against the eager result,
+with eager calls of the library between replays; a call that would upload its list is refused."""
+import numpy as np
+import pytest
+
+from kvgen import workloads
+from paper_2606_14779_amd import kvpool as K
+
+from gpu_util import check_full, make_run, say
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    yield
+    torch.cuda.synchronize()
+
+
+def _run(n):
+    rng = np.random.default_rng(n)
+    shape = workloads.KVShape("captured", 4, 2, 64)
+    regions = [workloads.RegionSpec("host", 1, 0), workloads.RegionSpec("staging", 2)]
+    req = workloads.RequestSpec(1, n, n, rng.permutation(n + 9)[:n].astype(np.int32),
+                                rng.permutation(n + 9)[:n].astype(np.int32))
+    wl = workloads.Workload(0, "captured", 93, shape, 0, regions, [req], n + 9, n + 9)
+    workloads._size_regions(wl.regions, [n], shape.block_bytes)
+    return make_run(wl)
+
+
+@pytest.mark.parametrize("call,n", [("retrieve", 20), ("store", 20), ("retrieve_noalloc", 20),
+                                    ("retrieve_noalloc", 400)])
+def test_replays_equal_the_eager_call(call, n):
+    say("case", call, n)
+    run = _run(n)
+    try:
+        host = run.setup(keep_host=True)
+        q = run.wl.requests[0]
+        store = call == "store"
+        cache = run.src if store else run.dst
+        table, slots = (q.src_slots, run.wl.src_num_slots) if store else (q.dst_slots, run.wl.dst_num_slots)
+        k, v = run.layer_ptrs(cache)
+
+        def enqueue():
+            getattr(run.pool, call)(run.maps[1], table, slots, k, v, torch.cuda.current_stream().cuda_stream)
+
+        enqueue()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            enqueue()
+        small = run.maps[1][:3]
+        for i in range(4):
+            run.fill_dst()
+            if store:
+                run.src.add_(1)   # other contents each time: the replay has to store these
+                host += np.uint16(1)
+            g.replay()
+            if store:
+                run.retrieve_all()
+            torch.cuda.synchronize()
+            check_full(run.wl, run, host)
+            # eager calls between the replays, on this and another stream; they land where they did
+            run.pool.retrieve(small, q.dst_slots[:3], run.wl.dst_num_slots, *run.layer_ptrs(run.dst),
+                              torch.cuda.current_stream().cuda_stream)
+            side = torch.cuda.Stream()
+            side.wait_stream(torch.cuda.current_stream())
+            run.pool.retrieve(small, q.dst_slots[:3], run.wl.dst_num_slots, *run.layer_ptrs(run.dst), side.cuda_stream)
+            torch.cuda.synchronize()
+        run.pool.release(1)
+    finally:
+        run.close()
+
+
+def test_a_call_with_an_uploaded_list_is_refused():
+    run = _run(400)
+    try:
+        run.setup()
+        q = run.wl.requests[0]
+        k, v = run.layer_ptrs(run.dst)
+        x = torch.zeros(16, device="cuda")
+        g = torch.cuda.CUDAGraph()
+        codes = []
+        with torch.cuda.graph(g):
+            x.add_(1)
+            try:
+                run.pool.retrieve(run.maps[1], q.dst_slots, run.wl.dst_num_slots, k, v,
+                                  torch.cuda.current_stream().cuda_stream)
+            except K.KVPoolError as e:
+                codes.append(e.name)
+        assert codes == ["HIP"]
+        run.fill_dst()
+        before = run.dst.clone()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(run.dst, before)   # nothing of the refused call is in the graph
+    finally:
+        run.close()
+
+
+def test_thousands_of_calls_in_flight():
+    """More calls than completion events exist at first, over three streams; each request's release
+    waits for its own."""
+    run = _run(6)
+    try:
+        host = run.setup(keep_host=True)
+        streams = [torch.cuda.Stream() for _ in range(3)]
+        for s in streams:
+            s.wait_stream(torch.cuda.current_stream())
+        for i in range(3000):
+            run.retrieve(run.wl.requests[0], streams[i % 3])
+        torch.cuda.synchronize()
+        check_full(run.wl, run, host)
+        run.pool.release(1)
+    finally:
+        run.close()

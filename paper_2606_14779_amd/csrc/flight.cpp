@@ -1,13 +1,14 @@
 // Completion of store / retrieve calls.
 //
-// One event per call, recorded on the caller's stream after everything the call
-// enqueued, tells whoever has to wait (a later store of the same blocks, the
-// next call on the host link, a work-list buffer's next user, release, destroy)
-// that the call is done.  Everybody names the call by its number, and a number
-// below the oldest call still in flight needs no wait at all.  One record and
-// not one per purpose: each costs the stream about 5.5 us between two kernels
-// (a 2 MiB store over the link left 13.4 us of gap with three records, a
-// retrieve 8 with two, an HBM-only retrieve 2.4 with one).
+// One event per call, complete when everything the call enqueued is, tells
+// whoever has to wait (a later store of the same blocks, the next call on the
+// host link, a work-list buffer's next user, release, destroy) that the call is
+// done.  Everybody names the call by its number, and a number below the oldest
+// call still in flight needs no wait at all.  A call of one kernel gives the
+// event to its launch, where it costs nothing; recorded after the work it is a
+// packet between this call's kernel and the next one's (a 2 MiB store over the
+// link left 13.4 us of gap with three records, a retrieve 8 with two, an
+// HBM-only retrieve 2.4 with one).
 
 #include "internal.hpp"
 
@@ -19,7 +20,7 @@ constexpr size_t kMaxFlight = 4096;   // calls in flight before a further one wa
 
 void land(Pool &p)   // the oldest call is done
 {
-    p.idle.push_back(p.flight.front().done);   // room reserved with the event
+    if (p.flight.front().owned) p.idle.push_back(p.flight.front().done);   // room reserved with the event
     p.flight.pop_front();
     ++p.flight_first;
 }
@@ -36,7 +37,9 @@ void add_idle_event(Pool &p)
 
 const FlightRec *in_flight(const Pool &p, uint64_t call)
 {
-    return call < p.flight_first ? nullptr : &p.flight[call - p.flight_first];
+    if (call < p.flight_first) return nullptr;
+    const FlightRec &f = p.flight[call - p.flight_first];
+    return f.done ? &f : nullptr;
 }
 
 void wait_call(const Pool &p, uint64_t call)
@@ -49,40 +52,53 @@ void land_done_calls(Pool &p)
     // a query that finds work pending leaves "not ready" as the thread's last
     // error, so it must not run over an error that the caller has yet to read
     while (!p.flight.empty() && hipPeekAtLastError() == hipSuccess) {
-        const hipError_t q = hipEventQuery(p.flight.front().done);
-        if (q != hipSuccess) {
-            clear_hip_error();
-            if (q != hipErrorNotReady) check_hip(q, "hipEventQuery");
-            break;
+        if (p.flight.front().done) {
+            const hipError_t q = hipEventQuery(p.flight.front().done);
+            if (q != hipSuccess) {
+                clear_hip_error();
+                if (q != hipErrorNotReady) check_hip(q, "hipEventQuery");
+                break;
+            }
         }
         land(p);
     }
 }
 
-uint64_t record_call(Pool &p, hipStream_t s, bool may_create)
+hipEvent_t begin_call(Pool &p, hipStream_t s, hipEvent_t lent)
 {
+    if (lent) {
+        p.flight.push_back(FlightRec{lent, s, false});
+        return lent;
+    }
     if (p.idle.empty()) {
-        if (may_create && p.flight.size() < kMaxFlight) {
+        if (p.flight.size() < kMaxFlight) {
             add_idle_event(p);
         } else {
-            check_hip(hipEventSynchronize(p.flight.front().done), "hipEventSynchronize");
-            land(p);
+            while (p.idle.empty()) {
+                if (p.flight.front().done) check_hip(hipEventSynchronize(p.flight.front().done), "hipEventSynchronize");
+                land(p);
+            }
         }
     }
-    p.flight.push_back(FlightRec{p.idle.back(), s});
-    const hipError_t e = hipEventRecord(p.idle.back(), s);
-    if (e != hipSuccess) {
-        p.flight.pop_back();
-        check_hip(e, "hipEventRecord");
-    }
+    p.flight.push_back(FlightRec{p.idle.back(), s, true});
     p.idle.pop_back();
-    return p.flight_first + p.flight.size() - 1;
+    return p.flight.back().done;
 }
+
+void cancel_call(Pool &p) noexcept
+{
+    if (p.flight.back().owned) p.idle.push_back(p.flight.back().done);
+    p.flight.pop_back();
+}
+
+uint64_t last_call(const Pool &p) { return p.flight_first + p.flight.size() - 1; }
 
 void drain_calls(Pool &p) noexcept
 {
-    for (auto &f : p.flight) (void)hipEventSynchronize(f.done);
-    for (auto &f : p.flight) (void)hipEventDestroy(f.done);
+    for (auto &f : p.flight)
+        if (f.done) (void)hipEventSynchronize(f.done);
+    for (auto &f : p.flight)
+        if (f.owned) (void)hipEventDestroy(f.done);
     for (auto e : p.idle) (void)hipEventDestroy(e);
     p.flight.clear();
     p.idle.clear();

@@ -249,8 +249,9 @@ struct Slot {                    // one work-list buffer of the upload ring
 };
 
 struct FlightRec {               // one store / retrieve whose completion was not seen yet
-    hipEvent_t done;             // recorded on the caller's stream after all of it
+    hipEvent_t done;             // complete when all of it is; null: it is known to be
     hipStream_t stream;
+    bool owned;                  // the event goes back to the pool's idle ones
 };
 
 struct TimedCall {                // one store / retrieve recorded while timing is on
@@ -267,7 +268,8 @@ struct TimedCall {                // one store / retrieve recorded while timing 
 // which the host writes a call's list before the upload.  Calls take the two
 // halves in turn (a list larger than a half takes both), so that one call's
 // list is written while the previous call still reads its own; `free[h]` is
-// recorded after the kernels of the last call that used half h.
+// complete when the kernels of the last call that used half h are, and serves
+// as that call's completion event too.
 // Nothing here is ever released: each GPU keeps them until the process ends,
 // and no destructor makes a HIP call at exit.
 constexpr uint64_t kScratchBytes = 1ull << 20;
@@ -356,9 +358,13 @@ struct Pool {
 const FlightRec *in_flight(const Pool &p, uint64_t call);   // flight.cpp: null once it is known to be done
 void wait_call(const Pool &p, uint64_t call);               // host wait
 void land_done_calls(Pool &p);                              // notice finished calls (never under capture)
-// Number the call whose work was just enqueued on s.  Creates no event unless
-// may_create; may wait for the oldest call in flight.
-uint64_t record_call(Pool &p, hipStream_t s, bool may_create);
+// The completion event of the call about to end its work on s, which is call
+// last_call() from here on; `lent`: an event to use instead of one of the
+// pool's (no event is then created).  The caller records it (or gives it to a
+// launch), and takes the call back if that fails.
+hipEvent_t begin_call(Pool &p, hipStream_t s, hipEvent_t lent);
+void cancel_call(Pool &p) noexcept;
+uint64_t last_call(const Pool &p);
 void add_idle_event(Pool &p);
 void drain_calls(Pool &p) noexcept;                         // wait for every call, destroy the events
 void free_slot(Slot &s);                                    // pool.cpp: one work-list buffer
@@ -470,14 +476,15 @@ void plan_file(const FileGeometry &g, std::vector<HostBlock> &blocks, uint64_t s
 // gather: pool -> cache (retrieve); !gather: cache -> pool (store)
 constexpr uint32_t kClassRing = 2;
 constexpr uint32_t kClassFile = 4;   // a file regions' ring slot (pinned host memory)
+// done: an event that becomes the launch's completion (optional)
 hipError_t launch_chunk_copy(const CopyArgs &a, uint32_t cls, bool gather, uint32_t grid, uint32_t flags,
-                             hipStream_t s);
+                             hipStream_t s, hipEvent_t done = nullptr);
 // One launch of both classes of a call, of the f.a.n_items items in f.words
 // (f.a.items null: f.a.chunks pointers, then the items) or at f.a.items; the
 // host class's copy form comes from `flags`, the workgroups of each class from
 // its grid, capped at its units.
 hipError_t launch_call(CallArgs &f, bool gather, uint32_t grid_host, uint32_t grid_staging, uint32_t flags,
-                       hipStream_t s);
+                       hipStream_t s, hipEvent_t done);
 hipError_t launch_list_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s);   // bytes: multiple of 16
 hipError_t launch_probe_copy(void *dst, const void *src, uint64_t bytes, uint32_t grid,
                              uint32_t flags, hipStream_t s);

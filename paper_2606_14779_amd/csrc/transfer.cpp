@@ -437,26 +437,55 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     // ordering with earlier work on the same requests from any stream:
     // retrieve after store (read after write), store after store/retrieve
     for (RequestRec *rec : touched) wait_for(gather ? rec->stored_call : rec->busy_call);
-    // one host-class kernel on the link at a time, in enqueue order: two of
-    // them would only share its bandwidth and both end late
-    auto take_link = [&] { wait_for(p.link_call[op]); };
     // The call's completion.  busy must cover every call still touching the
     // request, not only this one: two retrieves of a request may run on
     // different streams at once, and release, destroy and a later store wait on
     // busy alone.  So when the previous one was on another stream, the caller's
     // stream first waits for it (after this call's kernels, so only later work
     // on the stream is held back), and the new one covers both.
-    Slot *slot = nullptr;   // the call's work-list buffer, once it is in use
-    auto finish = [&](bool on_link) {
-        if (capturing) return;
-        for (RequestRec *rec : touched) wait_for(rec->busy_call);
-        const uint64_t call = record_call(p, s, !noalloc);
+    Slot *slot = nullptr;        // the call's work-list buffer, once it is in use
+    hipEvent_t lent = nullptr;   // the allocation-free call's event
+    auto touch = [&](bool on_link) {   // the call is last_call()
+        const uint64_t call = last_call(p);
         if (slot) slot->call = call;
         if (on_link) p.link_call[op] = call;
         for (RequestRec *rec : touched) {
             rec->busy_call = call;
             if (!gather) rec->stored_call = call;
         }
+    };
+    auto finish = [&](bool on_link) {   // everything is enqueued: record it
+        if (capturing) return;
+        for (RequestRec *rec : touched) wait_for(rec->busy_call);
+        const hipEvent_t done = begin_call(p, s, lent);
+        const hipError_t e = hipEventRecord(done, s);
+        if (e != hipSuccess) {
+            cancel_call(p);
+            check_hip(e, "hipEventRecord");
+        }
+        touch(on_link);
+    };
+    // The call's only kernel, with the completion as its own event, unless work
+    // on another stream has to be waited for in between.
+    auto launch_last = [&](bool on_link, auto &&kernel) {
+        bool covers = !capturing;
+        for (RequestRec *rec : touched) {
+            const FlightRec *f = in_flight(p, rec->busy_call);
+            covers = covers && !(f && f->stream != s && rec->busy_call != waited);
+        }
+        if (on_link) wait_for(p.link_call[op]);   // one host-class kernel on the link at a time, in enqueue
+                                                  // order: two would only share its bandwidth and both end late
+        if (!covers) {
+            check_hip(kernel(nullptr), "kernel launch");
+            finish(on_link);
+            return;
+        }
+        const hipError_t e = kernel(begin_call(p, s, lent));
+        if (e != hipSuccess) {
+            cancel_call(p);
+            check_hip(e, "kernel launch");
+        }
+        touch(on_link);
     };
 
     const uint32_t chunks = 2 * (layer_end - layer_begin);
@@ -484,7 +513,9 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     // with 8 workgroups).  In two launches the internal stream takes the staging
     // class, for enough of its bytes.
     const bool lds = p.spec.pool_layout == 1 && (lh.flags & KVP_LAUNCH_LDS) != 0;
-    const bool one_launch = batches.empty() && (noalloc || !p.timing) && !(lds && p.chunk_bytes > kMergeLdsMax);
+    const bool both = host && !items[KVP_CLASS_STAGING].empty();
+    const bool one_launch =
+        batches.empty() && (noalloc || !p.timing) && !(both && lds && p.chunk_bytes > kMergeLdsMax);
     const bool large = batches.empty() && items[KVP_CLASS_STAGING].size() * width >= kForkMinBytes;
     const bool fork_staging = large && host && !one_launch;
     const FlightRec *storing = in_flight(p, p.link_call[KVP_OP_STORE]);
@@ -514,9 +545,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         auto *list = reinterpret_cast<CopyItem *>(f.words + chunks);
         std::copy(items[0].begin(), items[0].end(), list);
         std::copy(items[1].begin(), items[1].end(), list + items[0].size());
-        if (host) take_link();
-        check_hip(launch_call(f, gather, lh.grid, ls.grid, lh.flags, s), "kernel launch");
-        finish(host);
+        launch_last(host, [&](hipEvent_t done) { return launch_call(f, gather, lh.grid, ls.grid, lh.flags, s, done); });
         return;
     }
 
@@ -537,8 +566,13 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         // a half is rewritten, in either memory, only after the kernels of the
         // last call that used it (from any pool, on any stream)
         half = whole ? 0 : sd->next;
-        for (uint32_t h = 0; h < 2; ++h)
-            if ((whole || h == half) && sd->free_rec[h]) check_hip(hipEventSynchronize(sd->free[h]), "hipEventSynchronize");
+        for (uint32_t h = 0; h < 2; ++h) {
+            if (!(whole || h == half) || !sd->free_rec[h]) continue;
+            check_hip(hipEventSynchronize(sd->free[h]), "hipEventSynchronize");
+            for (auto &f : p.flight)   // the event's next use is another call's
+                if (f.done == sd->free[h]) f.done = nullptr;
+        }
+        lent = sd->free[half];
         host_list = static_cast<char *>(sd->host) + half * (kScratchBytes / 2);
         host_list_dev = static_cast<char *>(sd->host_dev) + half * (kScratchBytes / 2);
         dev_base = static_cast<char *>(sd->dev) + half * (kScratchBytes / 2);
@@ -556,14 +590,14 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
 
     check_hip(launch_list_copy(dev_base, host_list_dev, bytes, s), "kernel launch");
     slot = buffer;   // from here on the buffer is in use even if a launch fails
-    auto free_scratch = [&] {   // after the call's kernels
+    auto took_scratch = [&] {   // after finish or launch_last, which used free[half]
         if (!noalloc || capturing) return;
-        for (uint32_t h = 0; h < 2; ++h) {
-            if (!whole && h != half) continue;
-            check_hip(hipEventRecord(sd->free[h], s), "hipEventRecord");
-            sd->free_rec[h] = true;
-        }
+        sd->free_rec[half] = true;
         sd->next = half ^ 1u;
+        if (whole) {
+            check_hip(hipEventRecord(sd->free[1], s), "hipEventRecord");
+            sd->free_rec[1] = true;
+        }
     };
     // After a failure once the work list is on its way (a file read or write
     // that fails, a launch or copy the runtime refuses), whatever was enqueued
@@ -576,13 +610,14 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         (void)hipEventRecord(p.stage_done, p.s_stage);
         (void)hipStreamWaitEvent(s, p.stage_done, 0);
         try {
-            free_scratch();
             finish(host);
+            took_scratch();
         } catch (...) {
             (void)hipStreamSynchronize(s);   // nothing was recorded to wait for
         }
         clear_hip_error();
     };
+    bool finished = false;   // the last launch carried the call's completion
     auto enqueue = [&] {
         if (fork_staging || !batches.empty() || !file_batches.empty())
             check_hip(hipEventRecord(p.fork, s), "hipEventRecord");
@@ -612,13 +647,18 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             }
         };
         const bool staging = !items[KVP_CLASS_STAGING].empty();
-        if (one_launch && host && staging) {
+        if (one_launch && file_batches.empty()) {
             CallArgs f = {};
             f.a = args[KVP_CLASS_HOST];
             f.a.n_items += args[KVP_CLASS_STAGING].n_items;
             f.n_host = args[KVP_CLASS_HOST].n_items;
-            take_link();
-            check_hip(launch_call(f, gather, lh.grid, ls.grid, lh.flags, s), "kernel launch");
+            launch_last(host, [&](hipEvent_t done) {
+                if (host && staging) return launch_call(f, gather, lh.grid, ls.grid, lh.flags, s, done);
+                const uint32_t c = host ? KVP_CLASS_HOST : KVP_CLASS_STAGING;
+                const LaunchCfg &lc = host ? lh : ls;
+                return launch_chunk_copy(args[c], c, gather, lc.grid, lc.flags, s, done);
+            });
+            finished = true;
         } else if (batches.empty()) {
             if (fork_staging) {
                 check_hip(hipStreamWaitEvent(p.s_stage, p.fork, 0), "hipStreamWaitEvent");
@@ -628,7 +668,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
                 launch(KVP_CLASS_STAGING, s);   // small: in order on the caller's stream
             }
             if (host) {
-                take_link();
+                wait_for(p.link_call[op]);   // in turn, as in launch_last
                 launch(KVP_CLASS_HOST, s);
             }
             if (fork_staging) check_hip(hipStreamWaitEvent(s, p.stage_done, 0), "hipStreamWaitEvent");
@@ -718,8 +758,8 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         settle();
         throw;
     }
-    free_scratch();
-    finish(host && batches.empty());
+    if (!finished) finish(host && batches.empty());
+    took_scratch();
 }
 
 }  // namespace kvp

@@ -444,7 +444,9 @@ int kv_pool_set_bandwidths(kvp_pool *pool, const uint64_t *bandwidths);
  * of one (class, op) kernel; flags replace the current ones.  Defaults: host
  * class 12 workgroups (token-major pool: 16, 20 for the store); staging class
  * one workgroup per 4 KiB moved, up to 2^23 (the launch caps a grid at the
- * call's own workgroups), with KVP_LAUNCH_NT_LOAD | KVP_LAUNCH_NT_STORE;
+ * call's own workgroups), with KVP_LAUNCH_NT_LOAD | KVP_LAUNCH_NT_STORE (no
+ * KVP_LAUNCH_NT_LOAD for a pool_layout 1 pool whose rows, D*elem_bytes, are no
+ * multiple of 64 bytes);
  * KVP_LAUNCH_NT_STORE for the host-class store; KVP_LAUNCH_LDS for the
  * host-class retrieve of a pool_layout 1 pool.  With the default host-class
  * store grid, a store whose staging class takes longer than its host class
@@ -485,7 +487,7 @@ int kv_pool_set_bandwidths(kvp_pool *pool, const uint64_t *bandwidths);
  * in the kernel arguments of the one launch of both classes: workgroups up
  * to each class's grid (capped at its units), the host class in the copy form
  * of its flags without KVP_LAUNCH_XCD, KVP_LAUNCH_CHUNK_MAJOR and
- * KVP_LAUNCH_TILE, the staging class in its default form.  This saves the
+ * KVP_LAUNCH_TILE, the staging class with non-temporal stores.  This saves the
  * work-list upload (about 10 microseconds on MI355X); for a full 32-layer
  * range it covers up to 160 blocks.
  * KVP_LAUNCH_UPLOAD on either class of the op turns it off (the list is

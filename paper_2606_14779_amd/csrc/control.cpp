@@ -158,10 +158,14 @@ void measure_regions(Pool &p, uint64_t probe_bytes, uint32_t flags, uint64_t *mb
             hipStream_t st = p.s_stage;   // one probe at a time
             const uint64_t n = probe_span(reg, probe_bytes);
             const LaunchCfg &lc = p.launch[cls][KVP_OP_RETRIEVE];
+            // a contiguous copy shares no lines: non-temporal unless the caller chose the flags
+            const uint32_t hint = lc.flags == default_flags(cls, KVP_OP_RETRIEVE, p.spec) && cls == KVP_CLASS_STAGING
+                                      ? KVP_LAUNCH_NT_LOAD
+                                      : lc.flags & KVP_LAUNCH_NT_LOAD;
             float best = 0.f;
             for (int it = 0; it < 4; ++it) {
                 check_hip(hipEventRecord(e0, st), "hipEventRecord");
-                check_hip(launch_probe_copy(scratch, reg.dev, n, lc.grid, lc.flags & KVP_LAUNCH_NT_LOAD, st),
+                check_hip(launch_probe_copy(scratch, reg.dev, n, lc.grid, hint, st),
                           "probe launch");
                 check_hip(hipEventRecord(e1, st), "hipEventRecord");
                 check_hip(hipEventSynchronize(e1), "hipEventSynchronize");

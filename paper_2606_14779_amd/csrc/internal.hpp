@@ -416,6 +416,7 @@ struct CallArgs {
     CopyArgs a;                // geometry; a.n_items = all items; a.items, a.cache null: the list is in words
     uint32_t n_host;           // items [0, n_host) are host-class, the rest staging-class
     uint32_t grid_host;        // workgroups taking the host-class items
+    uint32_t cached_loads;     // 1: token-major staging loads are not non-temporal
     uint64_t words[kInlineWords];
 };
 // passed by value as the kernel's only argument: it must fit the 4 KiB kernel-argument segment
@@ -481,10 +482,10 @@ hipError_t launch_chunk_copy(const CopyArgs &a, uint32_t cls, bool gather, uint3
                              hipStream_t s, hipEvent_t done = nullptr);
 // One launch of both classes of a call, of the f.a.n_items items in f.words
 // (f.a.items null: f.a.chunks pointers, then the items) or at f.a.items; the
-// host class's copy form comes from `flags`, the workgroups of each class from
-// its grid, capped at its units.
+// host class's copy form comes from `flags`, the staging class's load hint from
+// staging_flags, the workgroups of each class from its grid, capped at its units.
 hipError_t launch_call(CallArgs &f, bool gather, uint32_t grid_host, uint32_t grid_staging, uint32_t flags,
-                       hipStream_t s, hipEvent_t done);
+                       uint32_t staging_flags, hipStream_t s, hipEvent_t done);
 hipError_t launch_list_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s);   // bytes: multiple of 16
 hipError_t launch_probe_copy(void *dst, const void *src, uint64_t bytes, uint32_t grid,
                              uint32_t flags, hipStream_t s);

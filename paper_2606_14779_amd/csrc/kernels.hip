@@ -442,7 +442,8 @@ __global__ __launch_bounds__(kThreads) void file_slot_copy(CopyArgs a)
 // Both classes of a call in one launch: workgroups [0, grid_host) take the
 // host-class items, the others the staging-class items, so the two run side by
 // side with no second stream and no events between.  FORM to NTS are the host
-// class's copy form; the staging class takes its own body.  The table and the
+// class's copy form; the staging class takes its own body with non-temporal
+// stores, and loads too unless cached_loads.  The table and the
 // items are read with scalar loads, from the kernel arguments (a small call) or
 // from the uploaded work list.  The class split is uniform per workgroup.
 template <bool GATHER, int FORM, int UNROLL, bool NTL, bool NTS>
@@ -466,8 +467,11 @@ __global__ __launch_bounds__(kThreads) void both_regions_copy(CallArgs f)
         chunk_copy_body<GATHER, FORM, UNROLL, NTL, NTS>(a, items, table, blockIdx.x, f.grid_host);
     } else if (blockIdx.x >= first) {
         a.n_items = f.a.n_items - f.n_host;
-        wave_copy_body<GATHER, FORM != kPlain, true, true>(a, items + f.n_host, table, blockIdx.x - first,
-                                                           gridDim.x - first);
+        const uint32_t g = blockIdx.x - first, G = gridDim.x - first;
+        if (FORM != kPlain && f.cached_loads)
+            wave_copy_body<GATHER, FORM != kPlain, false, true>(a, items + f.n_host, table, g, G);
+        else
+            wave_copy_body<GATHER, FORM != kPlain, true, true>(a, items + f.n_host, table, g, G);
     }
 }
 
@@ -701,8 +705,8 @@ hipError_t launch_chunk_copy(const CopyArgs &args, uint32_t cls, bool gather, ui
                   : launch_dir<kClassFile, false>(a, grid, flags, s, done);
 }
 
-hipError_t launch_call(CallArgs &f, bool gather, uint32_t grid_host, uint32_t grid_staging,
-                             uint32_t flags, hipStream_t s, hipEvent_t done)
+hipError_t launch_call(CallArgs &f, bool gather, uint32_t grid_host, uint32_t grid_staging, uint32_t flags,
+                       uint32_t staging_flags, hipStream_t s, hipEvent_t done)
 {
     CopyArgs &a = f.a;
     if (a.n_items == 0) return hipSuccess;
@@ -718,6 +722,7 @@ hipError_t launch_call(CallArgs &f, bool gather, uint32_t grid_host, uint32_t gr
         wave_units(a, n_staging, gather);
         grid = (grid + kXcds - 1) / kXcds * kXcds + wave_grid(a, grid_staging);
     }
+    f.cached_loads = (staging_flags & KVP_LAUNCH_NT_LOAD) ? 0u : 1u;
     if (f.n_host == 0) flags &= ~KVP_LAUNCH_LDS;   // the staging class stages nothing through LDS
     return gather ? launch_dir<kClassBoth, true>(f, grid, flags, s, done)
                   : launch_dir<kClassBoth, false>(f, grid, flags, s, done);

@@ -545,7 +545,9 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         auto *list = reinterpret_cast<CopyItem *>(f.words + chunks);
         std::copy(items[0].begin(), items[0].end(), list);
         std::copy(items[1].begin(), items[1].end(), list + items[0].size());
-        launch_last(host, [&](hipEvent_t done) { return launch_call(f, gather, lh.grid, ls.grid, lh.flags, s, done); });
+        launch_last(host, [&](hipEvent_t done) {
+            return launch_call(f, gather, lh.grid, ls.grid, lh.flags, ls.flags, s, done);
+        });
         return;
     }
 
@@ -653,7 +655,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             f.a.n_items += args[KVP_CLASS_STAGING].n_items;
             f.n_host = args[KVP_CLASS_HOST].n_items;
             launch_last(host, [&](hipEvent_t done) {
-                if (host && staging) return launch_call(f, gather, lh.grid, ls.grid, lh.flags, s, done);
+                if (both) return launch_call(f, gather, lh.grid, ls.grid, lh.flags, ls.flags, s, done);
                 const uint32_t c = host ? KVP_CLASS_HOST : KVP_CLASS_STAGING;
                 const LaunchCfg &lc = host ? lh : ls;
                 return launch_chunk_copy(args[c], c, gather, lc.grid, lc.flags, s, done);

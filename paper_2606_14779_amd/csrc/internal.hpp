@@ -298,6 +298,45 @@ constexpr uint64_t kBounceSlotMin = 1ull << 30;      //   default bytes per slot
 constexpr uint32_t kFileSlots = 2;                   // file regions: pinned ring slots
 constexpr uint64_t kFileSlotMax = 256ull << 20;      //   default bytes per slot (one block at least)
 
+struct CopyItem {          // 16 bytes, one block of work
+    uint64_t pool;         // device-visible address of the block in its region
+    uint32_t slot;         // engine-cache slot
+    uint32_t region;       // host side only: the region it lies in (0 in a ring slot)
+};
+
+// Where a call's map entries are in one region: the range of the last one, and
+// where the next one lies if it follows it.
+struct RegionPlace {
+    const Allocation *alloc = nullptr;
+    uint64_t next = 0, end = 0;   // offset of the next block; end of the range
+    uint64_t index = 0;           // of the last block in its range
+    uint64_t word = 0;            // store: first word of the range's bitmap
+};
+
+// Buffers of a call's plan.  The pool keeps them (its lock is held throughout a
+// call): allocated anew they cost a call of 8192 blocks their page faults.
+struct Plan {
+    std::vector<CopyItem> items[2], other;   // per class; the sort's other buffer
+    std::vector<RequestRec *> touched;       // requests of the call, each once
+    std::vector<uint64_t> seen;              // bitmaps of the places written
+    std::vector<uint32_t> wide_slots;
+    std::vector<RegionPlace> places;         // per region
+    void reset(size_t regions)
+    {
+        clear(items[0]), clear(items[1]), clear(other), clear(touched), clear(seen), clear(wide_slots), clear(places);
+        places.resize(regions);
+    }
+
+private:
+    static constexpr size_t kKeep = 1u << 20;   // entries kept of each
+    template <class T>
+    static void clear(std::vector<T> &v)
+    {
+        v.clear();
+        if (v.capacity() > kKeep) v.shrink_to_fit();
+    }
+};
+
 struct Pool {
     int device = -1;
     bool placement_only = true;
@@ -310,6 +349,7 @@ struct Pool {
     Glt glt;
     uint32_t next_gen = 1;
     uint64_t call_epoch = 0;        // numbers the store / retrieve calls
+    Plan plan;
     mutable std::mutex mu;
 
     hipStream_t s_stage = nullptr;     // the staging-class kernel's stream (host class: caller's);
@@ -376,12 +416,6 @@ void free_file_ring(Pool &p);                               // pool.cpp: after t
 void drain_timed(Pool &p, kvp_timing_summary *sum);        // transfer.cpp: wait, summarise, recycle
 
 // ---------------------------------------------------------------- kernels (kernels.hip)
-
-struct CopyItem {          // 16 bytes, one block of work
-    uint64_t pool;         // device-visible address of the block in its region
-    uint32_t slot;         // engine-cache slot
-    uint32_t region;       // host side only: the region it lies in (0 in a ring slot)
-};
 
 struct CopyArgs {
     const CopyItem *items;     // device

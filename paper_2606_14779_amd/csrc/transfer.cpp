@@ -88,7 +88,7 @@ const Allocation *resolve(const Pool &p, const kvp_loc &e, uint32_t b, const All
 // shaped blocks retrieved with a permuted table: 5321 GB/s in table order, 5901
 // in slot order; of 4096 Qwen3-shaped blocks stored: 6131 in map order, 6219
 // by region.  A radix sort on 11-bit digits: 2 passes cover 4M slots.
-void order_items(std::vector<CopyItem> &items, bool gather, uint32_t limit)
+void order_items(std::vector<CopyItem> &items, std::vector<CopyItem> &other, bool gather, uint32_t limit)
 {
     auto key = [gather](const CopyItem &i) { return gather ? i.slot : i.region; };
     auto less = [&](const CopyItem &x, const CopyItem &y) { return key(x) < key(y); };
@@ -98,7 +98,7 @@ void order_items(std::vector<CopyItem> &items, bool gather, uint32_t limit)
         return;
     }
     constexpr uint32_t kDigit = 11, kMask = (1u << kDigit) - 1;
-    std::vector<CopyItem> other(items.size());
+    other.resize(items.size());
     for (uint32_t shift = 0; shift < 32 && (limit - 1) >> shift; shift += kDigit) {
         uint32_t at[kMask + 1] = {};
         for (const CopyItem &i : items) ++at[key(i) >> shift & kMask];
@@ -295,23 +295,25 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     if (sdma && !p.bounce)   // only after a kv_pool_set_copy_ring that could not allocate
         fail(KVP_ERR_NOMEM, "copy-engine ring not allocated: set a smaller ring or clear KVP_LAUNCH_SDMA");
 
-    // GLT-resolved locations, grouped by region class (Sec. 4.3)
-    std::vector<CopyItem> items[2];
+    // GLT-resolved locations, grouped by region class (Sec. 4.3), in buffers that
+    // the pool keeps from call to call
+    Plan &plan = p.plan;
+    plan.reset(p.regions.size());
+    std::vector<CopyItem>(&items)[2] = plan.items;
     std::vector<HostBlock> host_blocks;   // copy-engine transport: placed in ring slots below
     std::vector<HostBlock> file_blocks;   // file regions: placed in the file ring's slots below
-    std::vector<RequestRec *> touched;
+    std::vector<RequestRec *> &touched = plan.touched;
     const uint64_t epoch = ++p.call_epoch;
     // No two present entries may write the same place: a destination slot on
     // retrieve, a pool block on store.  One pass over bitmaps -- of the
     // destination slots, or of the blocks of each allocation a store touches
     // (the block index within its allocation is exact after resolve) -- with
     // sorted slots only for a retrieve into far more slots than it moves.
-    std::vector<uint64_t> seen;
+    std::vector<uint64_t> &seen = plan.seen;
     const bool slot_bits = gather && num_slots <= std::max<uint64_t>(64ull * n_blocks, 1ull << 16);
     if (slot_bits) seen.assign((num_slots + 63) / 64, 0);
-    std::vector<uint32_t> wide_slots;
+    std::vector<uint32_t> &wide_slots = plan.wide_slots;
     std::unordered_map<const Allocation *, uint64_t> alloc_word;   // store: first bitmap word of an allocation
-    std::vector<uint64_t> region_word(p.regions.size(), 0);        // store: that of each region's hint
     bool dup = false;
     uint64_t dup_slot = 0;
     auto mark = [&](uint64_t bit) {
@@ -323,38 +325,46 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         }
         w |= m;
     };
-    // one hint per region: a request's blocks in a region share one range,
-    // while consecutive blocks of a striped map alternate between regions
-    std::vector<const Allocation *> hints(p.regions.size(), nullptr);
     for (uint32_t b = 0; b < n_blocks; ++b) {
         const kvp_loc &e = map[b];
         if (e.region == KVP_ABSENT) continue;
-        const Allocation *hint = resolve(p, e, b, e.region < hints.size() ? hints[e.region] : nullptr);
-        const bool new_hint = hint != hints[e.region];
-        hints[e.region] = hint;
+        // One place per region: a request's blocks in a region share one range,
+        // while consecutive blocks of a striped map alternate between regions.
+        // An entry that follows the last one in its range needs no further look.
+        RegionPlace *at = e.region < plan.places.size() ? &plan.places[e.region] : nullptr;
+        if (at && at->alloc && e.offset == at->next && e.offset < at->end && e.gen == at->alloc->gen) {
+            at->next += p.block_bytes;
+            ++at->index;
+        } else {
+            const Allocation *a = resolve(p, e, b, at ? at->alloc : nullptr);   // throws for a bad region
+            const bool other = a != at->alloc;
+            at->alloc = a;
+            at->index = (e.offset - a->base) / p.block_bytes;
+            at->next = e.offset + p.block_bytes;
+            at->end = a->base + a->blocks * p.block_bytes;
+            if (other && !gather) {
+                auto it = alloc_word.find(a);
+                if (it == alloc_word.end()) {
+                    it = alloc_word.emplace(a, seen.size()).first;
+                    seen.resize(seen.size() + (a->blocks + 63) / 64, 0);
+                }
+                at->word = it->second;
+            }
+            if (other && a->owner->call_mark != epoch) {   // each request listed once
+                a->owner->call_mark = epoch;
+                touched.push_back(a->owner);
+            }
+        }
         const int32_t slot = table[b];
         if (slot < 0 || static_cast<uint32_t>(slot) >= num_slots)
             fail(KVP_ERR_INVALID, "block table entry " + std::to_string(b) + " = " + std::to_string(slot) +
                                       " outside [0, " + std::to_string(num_slots) + ")");
-        if (slot_bits) {
+        if (slot_bits)
             mark(static_cast<uint64_t>(slot));
-        } else if (gather) {
+        else if (gather)
             wide_slots.push_back(static_cast<uint32_t>(slot));
-        } else {
-            if (new_hint) {
-                auto it = alloc_word.find(hint);
-                if (it == alloc_word.end()) {
-                    it = alloc_word.emplace(hint, seen.size()).first;
-                    seen.resize(seen.size() + (hint->blocks + 63) / 64, 0);
-                }
-                region_word[e.region] = it->second;
-            }
-            mark(region_word[e.region] * 64 + (e.offset - hint->base) / p.block_bytes);
-        }
-        if (new_hint && hint->owner->call_mark != epoch) {   // each request listed once
-            hint->owner->call_mark = epoch;
-            touched.push_back(hint->owner);
-        }
+        else
+            mark(at->word * 64 + at->index);
         const Region &r = p.regions[e.region];
         if (r.desc.type == KVP_REGION_FILE) {
             if (noalloc)
@@ -380,7 +390,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     if (dup)
         fail(KVP_ERR_INVALID, gather ? "destination slot " + std::to_string(dup_slot) + " named twice"
                                      : std::string("two map entries name the same pool block"));
-    order_items(items[KVP_CLASS_STAGING], gather, gather ? num_slots : static_cast<uint32_t>(p.regions.size()));
+    order_items(items[KVP_CLASS_STAGING], plan.other, gather, gather ? num_slots : static_cast<uint32_t>(p.regions.size()));
     const uint64_t width = 2ull * (layer_end - layer_begin) * p.chunk_bytes;   // bytes moved per block
     const uint64_t skip = 2ull * layer_begin * p.chunk_bytes;
     std::vector<LinkRun> runs;

@@ -4,11 +4,14 @@
 // whoever has to wait (a later store of the same blocks, the next call on the
 // host link, a work-list buffer's next user, release, destroy) that the call is
 // done.  Everybody names the call by its number, and a number below the oldest
-// call still in flight needs no wait at all.  A call of one kernel gives the
-// event to its launch, where it costs nothing; recorded after the work it is a
-// packet between this call's kernel and the next one's (a 2 MiB store over the
-// link left 13.4 us of gap with three records, a retrieve 8 with two, an
-// HBM-only retrieve 2.4 with one).
+// call still in flight needs no wait at all.  One record and not one per
+// purpose: each is a packet between this call's kernel and the next one's (a
+// 2 MiB store over the link left 13.4 us of gap with three records, a retrieve 8
+// with two, an HBM-only retrieve 2.4 with one).  Given to the launch as its stop
+// event it would cost the stream nothing (that store: 40.7 us a pass instead of
+// 43.8, back to back), but then every wait behind such a launch takes longer, up
+// to twice as long (33 MB out of HBM, each call waited for: 64.9 us instead of
+// 33.7), so it is recorded.
 
 #include "internal.hpp"
 

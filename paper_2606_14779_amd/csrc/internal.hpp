@@ -400,8 +400,8 @@ void wait_call(const Pool &p, uint64_t call);               // host wait
 void land_done_calls(Pool &p);                              // notice finished calls (never under capture)
 // The completion event of the call about to end its work on s, which is call
 // last_call() from here on; `lent`: an event to use instead of one of the
-// pool's (no event is then created).  The caller records it (or gives it to a
-// launch), and takes the call back if that fails.
+// pool's (no event is then created).  The caller records it, and takes the call
+// back if that fails.
 hipEvent_t begin_call(Pool &p, hipStream_t s, hipEvent_t lent);
 void cancel_call(Pool &p) noexcept;
 uint64_t last_call(const Pool &p);
@@ -511,15 +511,14 @@ void plan_file(const FileGeometry &g, std::vector<HostBlock> &blocks, uint64_t s
 // gather: pool -> cache (retrieve); !gather: cache -> pool (store)
 constexpr uint32_t kClassRing = 2;
 constexpr uint32_t kClassFile = 4;   // a file regions' ring slot (pinned host memory)
-// done: an event that becomes the launch's completion (optional)
 hipError_t launch_chunk_copy(const CopyArgs &a, uint32_t cls, bool gather, uint32_t grid, uint32_t flags,
-                             hipStream_t s, hipEvent_t done = nullptr);
+                             hipStream_t s);
 // One launch of both classes of a call, of the f.a.n_items items in f.words
 // (f.a.items null: f.a.chunks pointers, then the items) or at f.a.items; the
 // host class's copy form comes from `flags`, the staging class's load hint from
 // staging_flags, the workgroups of each class from its grid, capped at its units.
 hipError_t launch_call(CallArgs &f, bool gather, uint32_t grid_host, uint32_t grid_staging, uint32_t flags,
-                       uint32_t staging_flags, hipStream_t s, hipEvent_t done);
+                       uint32_t staging_flags, hipStream_t s);
 hipError_t launch_list_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s);   // bytes: multiple of 16
 hipError_t launch_probe_copy(void *dst, const void *src, uint64_t bytes, uint32_t grid,
                              uint32_t flags, hipStream_t s);

@@ -38,7 +38,6 @@
 // memory, filled or emptied by file reads and writes), and both_regions_copy
 // (both region classes of a call in one launch).
 
-#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
@@ -567,62 +566,53 @@ constexpr uint32_t kClassBoth = 3;   // dispatch only: both_regions_copy
 __device__ __host__ inline const CopyArgs &geometry(const CopyArgs &a) { return a; }
 __device__ __host__ inline const CopyArgs &geometry(const CallArgs &f) { return f.a; }
 
-// A launch; `done`, if any, becomes the event of its completion.  The event is
-// then the launch's own signal, which costs nothing: recorded after the launch
-// it is a packet of its own, with 2.7 us (idle caches) to 5.6 us of idle stream
-// before the next kernel.
-template <class A>
-static hipError_t launch(void (*kernel)(A), dim3 g, size_t lds, hipStream_t s, hipEvent_t done, const A &a)
-{
-    if (done)
-        hipExtLaunchKernelGGL(kernel, g, dim3(kThreads), lds, s, nullptr, done, 0, a);
-    else
-        hipLaunchKernelGGL(kernel, g, dim3(kThreads), lds, s, a);
-    return hipGetLastError();
-}
-
 template <uint32_t CLS, bool GATHER, int FORM, int UNROLL, bool NTL, bool NTS, class A>
-static hipError_t launch_one(const A &a, dim3 g, size_t lds, hipStream_t s, hipEvent_t done)
+static void launch_one(const A &a, dim3 g, size_t lds, hipStream_t s)
 {
     if constexpr (CLS == kClassBoth)
-        return launch<A>(both_regions_copy<GATHER, FORM, UNROLL, NTL, NTS>, g, lds, s, done, a);
+        hipLaunchKernelGGL((both_regions_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
     else if constexpr (CLS == KVP_CLASS_HOST)
-        return launch<A>(host_region_copy<GATHER, FORM, UNROLL, NTL, NTS>, g, lds, s, done, a);
+        hipLaunchKernelGGL((host_region_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
     else
-        return launch<A>(file_slot_copy<GATHER, FORM, UNROLL, NTL, NTS>, g, lds, s, done, a);
+        hipLaunchKernelGGL((file_slot_copy<GATHER, FORM, UNROLL, NTL, NTS>), g, dim3(kThreads), lds, s, a);
 }
 
 template <uint32_t CLS, bool GATHER, int FORM, int UNROLL, class A>
-static hipError_t launch_form(const A &a, uint32_t grid, uint32_t flags, size_t lds, hipStream_t s, hipEvent_t done)
+static hipError_t launch_form(const A &a, uint32_t grid, uint32_t flags, size_t lds, hipStream_t s)
 {
     const bool ntl = flags & KVP_LAUNCH_NT_LOAD, nts = flags & KVP_LAUNCH_NT_STORE;
     const dim3 g(grid);
-    if (ntl && nts) return launch_one<CLS, GATHER, FORM, UNROLL, true, true>(a, g, lds, s, done);
-    if (ntl) return launch_one<CLS, GATHER, FORM, UNROLL, true, false>(a, g, lds, s, done);
-    if (nts) return launch_one<CLS, GATHER, FORM, UNROLL, false, true>(a, g, lds, s, done);
-    return launch_one<CLS, GATHER, FORM, UNROLL, false, false>(a, g, lds, s, done);
+    if (ntl && nts)
+        launch_one<CLS, GATHER, FORM, UNROLL, true, true>(a, g, lds, s);
+    else if (ntl)
+        launch_one<CLS, GATHER, FORM, UNROLL, true, false>(a, g, lds, s);
+    else if (nts)
+        launch_one<CLS, GATHER, FORM, UNROLL, false, true>(a, g, lds, s);
+    else
+        launch_one<CLS, GATHER, FORM, UNROLL, false, false>(a, g, lds, s);
+    return hipGetLastError();
 }
 
 template <uint32_t CLS, bool GATHER, int FORM, class A>
-static hipError_t launch_unroll(const A &a, uint32_t grid, uint32_t flags, size_t lds, hipStream_t s, hipEvent_t done)
+static hipError_t launch_unroll(const A &a, uint32_t grid, uint32_t flags, size_t lds, hipStream_t s)
 {
     // enough 16-byte loads in flight per lane to cover the whole unit, up to 8
     const CopyArgs &geo = geometry(a);
     const uint64_t per_lane = (geo.chunk_bytes / geo.parts / 16 + kThreads - 1) / kThreads;
-    if (per_lane >= 8) return launch_form<CLS, GATHER, FORM, 8>(a, grid, flags, lds, s, done);
-    if (per_lane >= 4) return launch_form<CLS, GATHER, FORM, 4>(a, grid, flags, lds, s, done);
-    if (per_lane >= 2) return launch_form<CLS, GATHER, FORM, 2>(a, grid, flags, lds, s, done);
-    return launch_form<CLS, GATHER, FORM, 1>(a, grid, flags, lds, s, done);
+    if (per_lane >= 8) return launch_form<CLS, GATHER, FORM, 8>(a, grid, flags, lds, s);
+    if (per_lane >= 4) return launch_form<CLS, GATHER, FORM, 4>(a, grid, flags, lds, s);
+    if (per_lane >= 2) return launch_form<CLS, GATHER, FORM, 2>(a, grid, flags, lds, s);
+    return launch_form<CLS, GATHER, FORM, 1>(a, grid, flags, lds, s);
 }
 
 template <uint32_t CLS, bool GATHER, class A>
-static hipError_t launch_dir(const A &a, uint32_t grid, uint32_t flags, hipStream_t s, hipEvent_t done)
+static hipError_t launch_dir(const A &a, uint32_t grid, uint32_t flags, hipStream_t s)
 {
     const CopyArgs &geo = geometry(a);
-    if (geo.layout == 0) return launch_unroll<CLS, GATHER, kPlain>(a, grid, flags, 0, s, done);
+    if (geo.layout == 0) return launch_unroll<CLS, GATHER, kPlain>(a, grid, flags, 0, s);
     if ((flags & KVP_LAUNCH_LDS) && geo.chunk_bytes <= kMaxLdsChunk)
-        return launch_unroll<CLS, GATHER, kConvertLds>(a, grid, flags, geo.chunk_bytes, s, done);
-    return launch_unroll<CLS, GATHER, kConvert>(a, grid, flags, 0, s, done);
+        return launch_unroll<CLS, GATHER, kConvertLds>(a, grid, flags, geo.chunk_bytes, s);
+    return launch_unroll<CLS, GATHER, kConvert>(a, grid, flags, 0, s);
 }
 
 // Units of the HBM body and their order for a launch of n items.  Launches of
@@ -647,42 +637,41 @@ static uint32_t wave_grid(const CopyArgs &a, uint32_t grid)
 }
 
 template <uint32_t CLS, bool GATHER, bool TOKEN_MAJOR, bool NTL, bool NTS>
-static hipError_t launch_wave_one(const CopyArgs &a, dim3 g, hipStream_t s, hipEvent_t done)
+static hipError_t launch_wave_one(const CopyArgs &a, dim3 g, hipStream_t s)
 {
     if constexpr (CLS == KVP_CLASS_STAGING)
-        return launch<CopyArgs>(staging_region_copy<GATHER, TOKEN_MAJOR, NTL, NTS>, g, 0, s, done, a);
+        hipLaunchKernelGGL((staging_region_copy<GATHER, TOKEN_MAJOR, NTL, NTS>), g, dim3(kThreads), 0, s, a);
     else
-        return launch<CopyArgs>(ring_slot_copy<GATHER, TOKEN_MAJOR, NTL, NTS>, g, 0, s, done, a);
+        hipLaunchKernelGGL((ring_slot_copy<GATHER, TOKEN_MAJOR, NTL, NTS>), g, dim3(kThreads), 0, s, a);
+    return hipGetLastError();
 }
 
 template <uint32_t CLS, bool GATHER, bool TOKEN_MAJOR>
-static hipError_t launch_wave_nt(const CopyArgs &a, dim3 g, uint32_t flags, hipStream_t s, hipEvent_t done)
+static hipError_t launch_wave_nt(const CopyArgs &a, dim3 g, uint32_t flags, hipStream_t s)
 {
     const bool ntl = flags & KVP_LAUNCH_NT_LOAD, nts = flags & KVP_LAUNCH_NT_STORE;
-    if (ntl && nts) return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, true, true>(a, g, s, done);
-    if (ntl) return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, true, false>(a, g, s, done);
-    if (nts) return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, false, true>(a, g, s, done);
-    return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, false, false>(a, g, s, done);
+    if (ntl && nts) return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, true, true>(a, g, s);
+    if (ntl) return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, true, false>(a, g, s);
+    if (nts) return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, false, true>(a, g, s);
+    return launch_wave_one<CLS, GATHER, TOKEN_MAJOR, false, false>(a, g, s);
 }
 
 template <uint32_t CLS>
-static hipError_t launch_wave(CopyArgs a, bool gather, uint32_t grid, uint32_t flags, hipStream_t s, hipEvent_t done)
+static hipError_t launch_wave(CopyArgs a, bool gather, uint32_t grid, uint32_t flags, hipStream_t s)
 {
     wave_units(a, a.n_items, gather);
     const dim3 g(wave_grid(a, grid));
     if (a.layout == 0)
-        return gather ? launch_wave_nt<CLS, true, false>(a, g, flags, s, done)
-                      : launch_wave_nt<CLS, false, false>(a, g, flags, s, done);
-    return gather ? launch_wave_nt<CLS, true, true>(a, g, flags, s, done)
-                  : launch_wave_nt<CLS, false, true>(a, g, flags, s, done);
+        return gather ? launch_wave_nt<CLS, true, false>(a, g, flags, s) : launch_wave_nt<CLS, false, false>(a, g, flags, s);
+    return gather ? launch_wave_nt<CLS, true, true>(a, g, flags, s) : launch_wave_nt<CLS, false, true>(a, g, flags, s);
 }
 
 hipError_t launch_chunk_copy(const CopyArgs &args, uint32_t cls, bool gather, uint32_t grid, uint32_t flags,
-                             hipStream_t s, hipEvent_t done)
+                             hipStream_t s)
 {
     if (args.n_items == 0) return hipSuccess;
-    if (cls == KVP_CLASS_STAGING) return launch_wave<KVP_CLASS_STAGING>(args, gather, grid, flags, s, done);
-    if (cls == kClassRing) return launch_wave<kClassRing>(args, gather, grid, flags, s, done);
+    if (cls == KVP_CLASS_STAGING) return launch_wave<KVP_CLASS_STAGING>(args, gather, grid, flags, s);
+    if (cls == kClassRing) return launch_wave<kClassRing>(args, gather, grid, flags, s);
     CopyArgs a = args;
     // halves of a plain chunk are independent contiguous copies
     a.parts = (a.layout == 0 && (flags & KVP_LAUNCH_SPLIT2) && a.chunk_bytes % 32 == 0) ? 2u : 1u;
@@ -699,14 +688,13 @@ hipError_t launch_chunk_copy(const CopyArgs &args, uint32_t cls, bool gather, ui
         a.xcd_remap = (flags & KVP_LAUNCH_XCD) && grid % kXcds == 0 ? 1u : 0u;
     }
     if (cls == KVP_CLASS_HOST)
-        return gather ? launch_dir<KVP_CLASS_HOST, true>(a, grid, flags, s, done)
-                      : launch_dir<KVP_CLASS_HOST, false>(a, grid, flags, s, done);
-    return gather ? launch_dir<kClassFile, true>(a, grid, flags, s, done)
-                  : launch_dir<kClassFile, false>(a, grid, flags, s, done);
+        return gather ? launch_dir<KVP_CLASS_HOST, true>(a, grid, flags, s)
+                      : launch_dir<KVP_CLASS_HOST, false>(a, grid, flags, s);
+    return gather ? launch_dir<kClassFile, true>(a, grid, flags, s) : launch_dir<kClassFile, false>(a, grid, flags, s);
 }
 
 hipError_t launch_call(CallArgs &f, bool gather, uint32_t grid_host, uint32_t grid_staging, uint32_t flags,
-                       uint32_t staging_flags, hipStream_t s, hipEvent_t done)
+                       uint32_t staging_flags, hipStream_t s)
 {
     CopyArgs &a = f.a;
     if (a.n_items == 0) return hipSuccess;
@@ -724,8 +712,7 @@ hipError_t launch_call(CallArgs &f, bool gather, uint32_t grid_host, uint32_t gr
     }
     f.cached_loads = (staging_flags & KVP_LAUNCH_NT_LOAD) ? 0u : 1u;
     if (f.n_host == 0) flags &= ~KVP_LAUNCH_LDS;   // the staging class stages nothing through LDS
-    return gather ? launch_dir<kClassBoth, true>(f, grid, flags, s, done)
-                  : launch_dir<kClassBoth, false>(f, grid, flags, s, done);
+    return gather ? launch_dir<kClassBoth, true>(f, grid, flags, s) : launch_dir<kClassBoth, false>(f, grid, flags, s);
 }
 
 hipError_t launch_list_copy(void *dst, const void *src, uint64_t bytes, hipStream_t s)

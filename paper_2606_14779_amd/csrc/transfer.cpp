@@ -453,6 +453,9 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     // busy alone.  So when the previous one was on another stream, the caller's
     // stream first waits for it (after this call's kernels, so only later work
     // on the stream is held back), and the new one covers both.
+    // one host-class kernel on the link at a time, in enqueue order: two of
+    // them would only share its bandwidth and both end late
+    auto take_link = [&] { wait_for(p.link_call[op]); };
     Slot *slot = nullptr;        // the call's work-list buffer, once it is in use
     hipEvent_t lent = nullptr;   // the allocation-free call's event
     auto touch = [&](bool on_link) {   // the call is last_call()
@@ -475,29 +478,6 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         }
         touch(on_link);
     };
-    // The call's only kernel, with the completion as its own event, unless work
-    // on another stream has to be waited for in between.
-    auto launch_last = [&](bool on_link, auto &&kernel) {
-        bool covers = !capturing;
-        for (RequestRec *rec : touched) {
-            const FlightRec *f = in_flight(p, rec->busy_call);
-            covers = covers && !(f && f->stream != s && rec->busy_call != waited);
-        }
-        if (on_link) wait_for(p.link_call[op]);   // one host-class kernel on the link at a time, in enqueue
-                                                  // order: two would only share its bandwidth and both end late
-        if (!covers) {
-            check_hip(kernel(nullptr), "kernel launch");
-            finish(on_link);
-            return;
-        }
-        const hipError_t e = kernel(begin_call(p, s, lent));
-        if (e != hipSuccess) {
-            cancel_call(p);
-            check_hip(e, "kernel launch");
-        }
-        touch(on_link);
-    };
-
     const uint32_t chunks = 2 * (layer_end - layer_begin);
     CopyArgs geo = {};
     geo.chunks = chunks;
@@ -555,9 +535,9 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         auto *list = reinterpret_cast<CopyItem *>(f.words + chunks);
         std::copy(items[0].begin(), items[0].end(), list);
         std::copy(items[1].begin(), items[1].end(), list + items[0].size());
-        launch_last(host, [&](hipEvent_t done) {
-            return launch_call(f, gather, lh.grid, ls.grid, lh.flags, ls.flags, s, done);
-        });
+        if (host) take_link();
+        check_hip(launch_call(f, gather, lh.grid, ls.grid, lh.flags, ls.flags, s), "kernel launch");
+        finish(host);
         return;
     }
 
@@ -602,7 +582,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
 
     check_hip(launch_list_copy(dev_base, host_list_dev, bytes, s), "kernel launch");
     slot = buffer;   // from here on the buffer is in use even if a launch fails
-    auto took_scratch = [&] {   // after finish or launch_last, which used free[half]
+    auto took_scratch = [&] {   // after finish, which used free[half]
         if (!noalloc || capturing) return;
         sd->free_rec[half] = true;
         sd->next = half ^ 1u;
@@ -629,7 +609,6 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         }
         clear_hip_error();
     };
-    bool finished = false;   // the last launch carried the call's completion
     auto enqueue = [&] {
         if (fork_staging || !batches.empty() || !file_batches.empty())
             check_hip(hipEventRecord(p.fork, s), "hipEventRecord");
@@ -664,13 +643,12 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             f.a = args[KVP_CLASS_HOST];
             f.a.n_items += args[KVP_CLASS_STAGING].n_items;
             f.n_host = args[KVP_CLASS_HOST].n_items;
-            launch_last(host, [&](hipEvent_t done) {
-                if (both) return launch_call(f, gather, lh.grid, ls.grid, lh.flags, ls.flags, s, done);
-                const uint32_t c = host ? KVP_CLASS_HOST : KVP_CLASS_STAGING;
-                const LaunchCfg &lc = host ? lh : ls;
-                return launch_chunk_copy(args[c], c, gather, lc.grid, lc.flags, s, done);
-            });
-            finished = true;
+            if (host) take_link();
+            const uint32_t c = host ? KVP_CLASS_HOST : KVP_CLASS_STAGING;
+            const LaunchCfg &lc = host ? lh : ls;
+            check_hip(both ? launch_call(f, gather, lh.grid, ls.grid, lh.flags, ls.flags, s)
+                           : launch_chunk_copy(args[c], c, gather, lc.grid, lc.flags, s),
+                      "kernel launch");
         } else if (batches.empty()) {
             if (fork_staging) {
                 check_hip(hipStreamWaitEvent(p.s_stage, p.fork, 0), "hipStreamWaitEvent");
@@ -680,7 +658,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
                 launch(KVP_CLASS_STAGING, s);   // small: in order on the caller's stream
             }
             if (host) {
-                wait_for(p.link_call[op]);   // in turn, as in launch_last
+                take_link();
                 launch(KVP_CLASS_HOST, s);
             }
             if (fork_staging) check_hip(hipStreamWaitEvent(s, p.stage_done, 0), "hipStreamWaitEvent");
@@ -770,7 +748,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         settle();
         throw;
     }
-    if (!finished) finish(host && batches.empty());
+    finish(host && batches.empty());
     took_scratch();
 }
 

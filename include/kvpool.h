@@ -286,10 +286,11 @@ int kv_pool_retrieve(kvp_pool *pool, const kvp_loc *map, uint32_t n_blocks,
  *     its two halves in turn (a list larger than a half takes both); nothing
  *     in it needs to start at zero.  The library orders its users: the host
  *     waits, if need be, until the kernels of the last call that used the half
- *     (any pool, any stream) are done.  A graph that captured a call reads its
- *     list from the half when it is replayed, so it is valid until two further
- *     such calls were made on that GPU (one, for a list larger than a half);
- *     the list of a small call is part of the graph itself.
+ *     (any pool, any stream) are done.
+ *   - Under stream capture the array is not used: the whole list becomes part
+ *     of the graph, in the arguments of one launch per 160 present blocks or
+ *     so (32 layers), and a replay is not affected by any other call.  Replays
+ *     are the caller's to order; release does not wait for them.
  * Errors: as kv_pool_retrieve.
  */
 #define KVP_NOALLOC_SCRATCH_BYTES (1u << 20)

@@ -230,6 +230,35 @@ void run_file_batches(Pool &p, bool gather, const std::vector<FileBatch> &batche
     p.file_next = static_cast<uint32_t>((p.file_next + batches.size()) % kFileSlots);
 }
 
+// A call whose whole list travels in kernel arguments although one launch cannot
+// hold it: a series of launches on `s`, each with an equal share of both
+// classes' items, so that the two still run side by side, and of the moved
+// chunks too if these alone would fill the arguments (over 128 layers).
+void launch_in_parts(const CopyArgs &geo, const std::vector<CopyItem> (&items)[2], const std::vector<uint64_t> &table,
+                     bool gather, const LaunchCfg &lh, const LaunchCfg &ls, hipStream_t s)
+{
+    const uint32_t most_chunks = std::min(geo.chunks, 2 * kInlineWords / 3);
+    const uint64_t most_items = (kInlineWords - most_chunks) / 2;
+    const uint64_t n[2] = {items[0].size(), items[1].size()};
+    // each class's share is rounded up by less than one item
+    const uint64_t parts = (n[0] + n[1] + most_items - 2) / (most_items - 1);
+    for (uint32_t c = 0; c < geo.chunks; c += most_chunks)
+        for (uint64_t i = 0; i < parts; ++i) {
+            CallArgs f = {};
+            f.a = geo;
+            f.a.chunk0 += c;
+            f.a.chunks = std::min(most_chunks, geo.chunks - c);
+            std::copy(table.begin() + c, table.begin() + c + f.a.chunks, f.words);
+            auto *list = reinterpret_cast<CopyItem *>(f.words + f.a.chunks), *end = list;
+            for (int cls = 0; cls < 2; ++cls) {
+                end = std::copy(items[cls].begin() + n[cls] * i / parts, items[cls].begin() + n[cls] * (i + 1) / parts, end);
+                if (cls == KVP_CLASS_HOST) f.n_host = static_cast<uint32_t>(end - list);
+            }
+            f.a.n_items = static_cast<uint32_t>(end - list);
+            check_hip(launch_call(f, gather, lh.grid, ls.grid, lh.flags, ls.flags, s), "kernel launch");
+        }
+}
+
 }  // namespace
 
 // Wait for every recorded call, optionally summarise it, and recycle its events.
@@ -433,9 +462,9 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     if (n_items == 0) return;
 
     hipStream_t s = static_cast<hipStream_t>(stream_ptr);
-    // A call may be captured into a graph if its work list travels in the kernel
-    // arguments or goes through the static scratch; its replays are the caller's
-    // to order, so nothing is recorded for it.
+    // A call may be captured into a graph if its work list travels in kernel
+    // arguments (a small call, and any allocation-free one); its replays are the
+    // caller's to order, so nothing is recorded for it.
     const bool capturing = stream_capturing(s);
     if (!capturing) land_done_calls(p);
     uint64_t waited = 0;
@@ -541,10 +570,20 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         return;
     }
 
+    if (capturing && noalloc) {
+        // A replay may run after any number of other calls that used the scratch,
+        // so a captured call's list goes where none of them writes: into the graph.
+        std::vector<uint64_t> table(chunks);
+        fill_table(table.data());
+        if (host) take_link();
+        launch_in_parts(geo, items, table, gather, lh, ls, s);
+        return;
+    }
+
     // work list: [chunks cache pointers][host items][staging items][file items], in a
     // ring slot of the pool, or in the device's static scratch (noalloc)
     const size_t bytes = list_bytes;
-    if (capturing && !noalloc)   // a replay would read a buffer that later calls rewrite
+    if (capturing)   // a replay would read a buffer that later calls rewrite
         fail(KVP_ERR_HIP, "a call with an uploaded work list: operation not permitted when stream is capturing");
     ScratchDevice *sd = nullptr;
     const bool whole = bytes > kScratchBytes / 2;   // of the scratch
@@ -583,7 +622,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     check_hip(launch_list_copy(dev_base, host_list_dev, bytes, s), "kernel launch");
     slot = buffer;   // from here on the buffer is in use even if a launch fails
     auto took_scratch = [&] {   // after finish, which used free[half]
-        if (!noalloc || capturing) return;
+        if (!noalloc) return;
         sd->free_rec[half] = true;
         sd->next = half ^ 1u;
         if (whole) {

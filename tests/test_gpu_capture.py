@@ -1,6 +1,6 @@
-"""Calls captured into a HIP graph: those whose work list travels in the kernel arguments, and the
-allocation-free retrieve through the static scratch.  Every replay is checked against the eager result,
-with eager calls of the library between replays; a call that would upload its list is refused."""
+"""Calls captured into a HIP graph: small ones, and allocation-free retrieves of any size, whose work
+lists both travel in kernel arguments.  Every replay is checked against the eager result, with eager calls
+of the library between replays; a call that would upload its list is refused."""
 import numpy as np
 import pytest
 
@@ -75,6 +75,58 @@ def test_replays_equal_the_eager_call(call, n):
         run.pool.release(1)
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("layers,heads,head_dim,layout", [(4, 2, 64, 0), (4, 2, 64, 1), (150, 1, 8, 0), (400, 1, 8, 1)])
+def test_captured_lists_are_not_shared(layers, heads, head_dim, layout):
+    """Two allocation-free calls with lists too large for one launch's arguments, captured into one graph,
+    and larger and smaller eager ones between capture and replay, on this and another pool: every replay
+    writes what the two calls named, and nothing else.  With 150 layers the engine pointers take most of
+    the arguments, with 400 they exceed them."""
+    rng = np.random.default_rng(layers)
+    shape = workloads.KVShape("captured", layers, heads, head_dim)
+    n = 420
+    regions = [workloads.RegionSpec("host", 1, 0), workloads.RegionSpec("staging", 2)]
+    say("case captured lists", layers, heads, head_dim, layout)
+
+    def one():
+        req = workloads.RequestSpec(1, n, n, rng.permutation(n + 9)[:n].astype(np.int32),
+                                    rng.permutation(n + 9)[:n].astype(np.int32))
+        wl = workloads.Workload(0, "captured", 95, shape, layout, list(regions), [req], n + 9, n + 9)
+        workloads._size_regions(wl.regions, [n], shape.block_bytes)
+        return make_run(wl)
+
+    run, other = one(), one()
+    try:
+        host = run.setup(keep_host=True)
+        other.setup()
+        q, m = run.wl.requests[0], run.maps[1]
+        k, v = run.layer_ptrs(run.dst)
+
+        def eager(r, count):
+            r.pool.retrieve_noalloc(r.maps[1][:count], r.wl.requests[0].dst_slots[::-1][:count].copy(),
+                                    r.wl.dst_num_slots, *r.layer_ptrs(r.dst), torch.cuda.current_stream().cuda_stream)
+
+        eager(run, n)   # both halves of the scratch are in use before the capture too
+        eager(run, 300)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            for part in (slice(0, 200), slice(200, n)):
+                run.pool.retrieve_noalloc(m[part], q.dst_slots[part].copy(), run.wl.dst_num_slots, k, v,
+                                          torch.cuda.current_stream().cuda_stream)
+        for count in (n, 300, 250):
+            eager(run, count)
+            eager(other, count)
+            torch.cuda.synchronize()
+            run.fill_dst()
+            g.replay()
+            torch.cuda.synchronize()
+            check_full(run.wl, run, host)
+        run.pool.release(1)
+    finally:
+        run.close()
+        other.close()
 
 
 def test_a_call_with_an_uploaded_list_is_refused():

@@ -468,10 +468,16 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     const bool capturing = stream_capturing(s);
     if (!capturing) land_done_calls(p);
     uint64_t waited = 0;
-    auto wait_for = [&](uint64_t call) {   // in stream order, so only for a call on another stream
+    // The stream of an earlier call may be this one, but its handle does not tell:
+    // hipStreamPerThread names another stream in every thread, and the handle of a
+    // destroyed stream is given out again.  The runtime knows the streams and drops
+    // a wait for work of the same one.  Under capture it refuses every wait for
+    // work outside of the graph, so there a handle that names one stream counts.
+    auto wait_for = [&](uint64_t call) {
         const FlightRec *f = call == waited ? nullptr : in_flight(p, call);
         waited = call;
-        if (f && f->stream != s) check_hip(hipStreamWaitEvent(s, f->done, 0), "hipStreamWaitEvent");
+        if (f && !(capturing && f->stream == s && s != hipStreamPerThread))
+            check_hip(hipStreamWaitEvent(s, f->done, 0), "hipStreamWaitEvent");
     };
     // ordering with earlier work on the same requests from any stream:
     // retrieve after store (read after write), store after store/retrieve

@@ -50,19 +50,23 @@ void wait_call(const Pool &p, uint64_t call)
     if (const FlightRec *f = in_flight(p, call)) check_hip(hipEventSynchronize(f->done), "hipEventSynchronize");
 }
 
+bool event_done(hipEvent_t e)
+{
+    // The query itself under the relaxed capture mode: beside a capture of
+    // another stream the runtime otherwise refuses it, and ends that capture too.
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    check_hip(hipThreadExchangeStreamCaptureMode(&mode), "hipThreadExchangeStreamCaptureMode");
+    const hipError_t q = hipEventQuery(e);
+    if (q != hipSuccess) clear_hip_error();   // "not ready" is the answer, not an error to leave behind
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (q != hipErrorNotReady) check_hip(q, "hipEventQuery");
+    return q == hipSuccess;
+}
+
 void land_done_calls(Pool &p)
 {
-    // a query that finds work pending leaves "not ready" as the thread's last
-    // error, so it must not run over an error that the caller has yet to read
     while (!p.flight.empty() && hipPeekAtLastError() == hipSuccess) {
-        if (p.flight.front().done) {
-            const hipError_t q = hipEventQuery(p.flight.front().done);
-            if (q != hipSuccess) {
-                clear_hip_error();
-                if (q != hipErrorNotReady) check_hip(q, "hipEventQuery");
-                break;
-            }
-        }
+        if (p.flight.front().done && !event_done(p.flight.front().done)) break;
         land(p);
     }
 }

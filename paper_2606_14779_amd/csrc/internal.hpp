@@ -397,6 +397,9 @@ struct Pool {
 
 const FlightRec *in_flight(const Pool &p, uint64_t call);   // flight.cpp: null once it is known to be done
 void wait_call(const Pool &p, uint64_t call);               // host wait
+// Query an event, beside a capture of another stream too.  It clears the thread's
+// last HIP error, so it must not run over one that the caller has yet to read.
+bool event_done(hipEvent_t e);
 void land_done_calls(Pool &p);                              // notice finished calls (never under capture)
 // The completion event of the call about to end its work on s, which is call
 // last_call() from here on; `lent`: an event to use instead of one of the

@@ -544,17 +544,11 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     const bool large = batches.empty() && items[KVP_CLASS_STAGING].size() * width >= kForkMinBytes;
     const bool fork_staging = large && host && !one_launch;
     const FlightRec *storing = in_flight(p, p.link_call[KVP_OP_STORE]);
+    // a store's host-class kernel not yet finished: the link carries traffic both ways
     if (gather && host && lh.default_grid && storing && lh.grid < kDuplexReadGrid && !capturing &&
-        hipPeekAtLastError() == hipSuccess) {   // never clear an error the caller has yet to read
-        // a store's host-class kernel not yet finished: the link carries traffic both ways
-        const hipError_t q = hipEventQuery(storing->done);
-        if (q == hipErrorNotReady) {
-            (void)hipGetLastError();   // "not ready" is the answer, not an error to leave behind
-            lh.grid = kDuplexReadGrid;
-        } else {
-            check_hip(q, "hipEventQuery");
-        }
-    }
+        hipPeekAtLastError() == hipSuccess &&   // never clear an error the caller has yet to read
+        !event_done(storing->done))
+        lh.grid = kDuplexReadGrid;
     if (!gather && host && large && lh.default_grid)
         lh.grid = throttled_store_grid(lh.grid, items[KVP_CLASS_HOST].size() * width,
                                        items[KVP_CLASS_STAGING].size() * width);

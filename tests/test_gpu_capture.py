@@ -1,6 +1,8 @@
 """Calls captured into a HIP graph: small ones, and allocation-free retrieves of any size, whose work
 lists both travel in kernel arguments.  Every replay is checked against the eager result, with eager calls
 of the library between replays; a call that would upload its list is refused."""
+from concurrent.futures import ThreadPoolExecutor
+
 import numpy as np
 import pytest
 
@@ -152,6 +154,44 @@ def test_a_call_with_an_uploaded_list_is_refused():
         torch.cuda.synchronize()
         assert torch.equal(run.dst, before)   # nothing of the refused call is in the graph
     finally:
+        run.close()
+
+
+@pytest.mark.parametrize("thread", ["same", "other"])
+@pytest.mark.parametrize("mode", ["global", "thread_local", "relaxed"])
+def test_small_calls_beside_a_capture(mode, thread):
+    """Eager small calls on one stream while another is being captured, from the capturing thread and from
+    another, with earlier calls in flight: they run, and the capture goes on unharmed."""
+    run = _run(20)
+    pool = ThreadPoolExecutor(1)
+    try:
+        host = run.setup(keep_host=True)
+        q = run.wl.requests[0]
+        side = torch.cuda.Stream()
+        dst, src = run.layer_ptrs(run.dst), run.layer_ptrs(run.src)
+        x = torch.zeros(16, device="cuda")
+        torch.cuda.synchronize()
+
+        def calls():
+            for i in range(40):   # more than the events that a pool starts with
+                run.pool.store(run.maps[1], q.src_slots, run.wl.src_num_slots, *src, side.cuda_stream)
+                run.pool.retrieve(run.maps[1], q.dst_slots, run.wl.dst_num_slots, *dst, side.cuda_stream)
+                run.pool.retrieve_noalloc(run.maps[1], q.dst_slots, run.wl.dst_num_slots, *dst, side.cuda_stream)
+
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, capture_error_mode=mode):
+            x.add_(1)
+            calls() if thread == "same" else pool.submit(calls).result()
+            x.add_(1)
+        torch.cuda.synchronize()
+        check_full(run.wl, run, host)
+        for i in range(3):
+            g.replay()
+            torch.cuda.synchronize()
+            assert bool((x == 2 * i + 2).all())
+        run.pool.release(1)
+    finally:
+        pool.shutdown()
         run.close()
 
 

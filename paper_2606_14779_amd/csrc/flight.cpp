@@ -19,7 +19,7 @@ namespace kvp {
 
 namespace {
 
-constexpr size_t kMaxFlight = 4096;   // calls in flight before a further one waits for the oldest
+constexpr size_t kMaxFlight = 4096;   // calls in flight from which on no event is created
 
 void land(Pool &p)   // the oldest call is done
 {
@@ -32,10 +32,31 @@ void land(Pool &p)   // the oldest call is done
 
 void add_idle_event(Pool &p)
 {
-    p.idle.reserve(p.flight.size() + p.idle.size() + 1);
+    p.idle.reserve(p.events + 1);
     hipEvent_t e = nullptr;
     check_hip(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
+    ++p.events;
     p.idle.push_back(e);
+}
+
+hipEvent_t take_request_event(Pool &p)
+{
+    if (p.idle.size() <= kIdleEvents) add_idle_event(p);
+    const hipEvent_t e = p.idle.back();
+    p.idle.pop_back();
+    return e;
+}
+
+void give_request_event(Pool &p, hipEvent_t e) noexcept
+{
+    forget_event(p, e);
+    p.idle.push_back(e);
+}
+
+void forget_event(Pool &p, hipEvent_t e) noexcept
+{
+    for (auto &f : p.flight)
+        if (f.done == e) f.done = nullptr;
 }
 
 const FlightRec *in_flight(const Pool &p, uint64_t call)
@@ -71,24 +92,17 @@ void land_done_calls(Pool &p)
     }
 }
 
-hipEvent_t begin_call(Pool &p, hipStream_t s, hipEvent_t lent)
+hipEvent_t begin_call(Pool &p, hipStream_t s, hipEvent_t lent, hipEvent_t own, bool may_create)
 {
-    if (lent) {
-        p.flight.push_back(FlightRec{lent, s, false});
-        return lent;
-    }
-    if (p.idle.empty()) {
-        if (p.flight.size() < kMaxFlight) {
+    if (!lent && p.idle.empty() && may_create && p.flight.size() < kMaxFlight) {
+        try {
             add_idle_event(p);
-        } else {
-            while (p.idle.empty()) {
-                if (p.flight.front().done) check_hip(hipEventSynchronize(p.flight.front().done), "hipEventSynchronize");
-                land(p);
-            }
+        } catch (const Error &) {   // the request's event will do
         }
     }
-    p.flight.push_back(FlightRec{p.idle.back(), s, true});
-    p.idle.pop_back();
+    if (!lent && p.idle.empty()) lent = own;
+    p.flight.push_back(FlightRec{lent ? lent : p.idle.back(), s, !lent});
+    if (!lent) p.idle.pop_back();
     return p.flight.back().done;
 }
 
@@ -106,6 +120,8 @@ void drain_calls(Pool &p) noexcept
         if (f.done) (void)hipEventSynchronize(f.done);
     for (auto &f : p.flight)
         if (f.owned) (void)hipEventDestroy(f.done);
+    for (auto &r : p.requests)
+        if (r.second->event) (void)hipEventDestroy(r.second->event);
     for (auto e : p.idle) (void)hipEventDestroy(e);
     p.flight.clear();
     p.idle.clear();

@@ -135,6 +135,7 @@ struct RequestRec {
     uint64_t stored_call = 0;       // the last store touching the request (see flight.cpp; 0: none)
     uint64_t busy_call = 0;         // the last store / retrieve touching it; each covers the one
                                     // before it, so its completion is that of every earlier call
+    hipEvent_t event = nullptr;     // for calls that find no idle one and may create none
     uint64_t call_mark = 0;         // the last store / retrieve call that listed it (pool lock held)
 };
 
@@ -358,7 +359,8 @@ struct Pool {
     // calls in flight, oldest first (flight.cpp); flight_first is the oldest's number
     std::deque<FlightRec> flight;
     uint64_t flight_first = 1;
-    std::vector<hipEvent_t> idle;       // events for later calls
+    std::vector<hipEvent_t> idle;       // events for later calls, with room for every one of the pool
+    size_t events = 0;                  // made so far: idle, of calls in flight, of requests
     // host link, per direction [op]: the last call with a host-class kernel; the
     // next one (any stream) waits for it, so calls take the link in turn
     uint64_t link_call[2] = {0, 0};
@@ -401,14 +403,20 @@ void wait_call(const Pool &p, uint64_t call);               // host wait
 // last HIP error, so it must not run over one that the caller has yet to read.
 bool event_done(hipEvent_t e);
 void land_done_calls(Pool &p);                              // notice finished calls (never under capture)
-// The completion event of the call about to end its work on s, which is call
-// last_call() from here on; `lent`: an event to use instead of one of the
-// pool's (no event is then created).  The caller records it, and takes the call
-// back if that fails.
-hipEvent_t begin_call(Pool &p, hipStream_t s, hipEvent_t lent);
-void cancel_call(Pool &p) noexcept;
+// The record and completion event of a call about to enqueue its work on s,
+// which is call last_call() from here on: `lent` if given; else one of the
+// pool's idle events, made if there is none and may_create; else `own`, the event
+// of a request of the call, which the call may always use: it records it only
+// after its stream waited for that request's earlier calls.  An event recorded
+// again makes earlier calls that hold it look done later, never sooner.
+hipEvent_t begin_call(Pool &p, hipStream_t s, hipEvent_t lent, hipEvent_t own, bool may_create);
+void cancel_call(Pool &p) noexcept;                         // nothing of it was enqueued, or all of it is done
 uint64_t last_call(const Pool &p);
+constexpr size_t kIdleEvents = 32;                          // made with the pool, besides the requests'
 void add_idle_event(Pool &p);
+hipEvent_t take_request_event(Pool &p);                     // leaves kIdleEvents idle ones, if calls hold none
+void give_request_event(Pool &p, hipEvent_t e) noexcept;    // its request's calls are done
+void forget_event(Pool &p, hipEvent_t e) noexcept;          // the calls that hold it are done
 void drain_calls(Pool &p) noexcept;                         // wait for every call, destroy the events
 void free_slot(Slot &s);                                    // pool.cpp: one work-list buffer
 void release_bounce(Pool &p);                               // pool.cpp: copy-engine ring, after its work

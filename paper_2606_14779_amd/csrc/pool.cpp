@@ -37,7 +37,6 @@ void check_hip(hipError_t e, const char *what)
 namespace {
 
 constexpr uint32_t kRingSlots = 32;
-constexpr uint32_t kFirstEvents = 32;   // completion events made with the pool (the allocation-free call makes none)
 constexpr uint64_t kCreateProbeBytes = 256ull << 20;   // per-region read probe when no bandwidths are given
 
 // Bind the calling thread's memory policy to one NUMA node for the scope.
@@ -468,7 +467,7 @@ Pool *pool_create(const kvp_region_desc *regions, const uint64_t *bandwidths, ui
         check_hip(hipEventCreateWithFlags(&p->fork, hipEventDisableTiming), "hipEventCreate");
         check_hip(hipEventCreateWithFlags(&p->stage_done, hipEventDisableTiming), "hipEventCreate");
         p->ring.resize(kRingSlots);
-        for (uint32_t i = 0; i < kFirstEvents; ++i) add_idle_event(*p);
+        for (size_t i = 0; i < kIdleEvents; ++i) add_idle_event(*p);
         (void)scratch_setup(hip_device);   // once per device: the static work-list scratch
         if (!bandwidths) {
             // Eq. 1 from measured bandwidths: each region's read rate into HBM
@@ -577,8 +576,13 @@ void pool_place(Pool &p, uint64_t request, uint32_t n_blocks, kvp_loc *out)
     RequestRec *r = rec.get();
     auto slot = p.requests.emplace(request, std::move(rec)).first;
     try {
+        if (!p.placement_only) {
+            DeviceScope dev(p.device);
+            r->event = take_request_event(p);
+        }
         commit_set(p, *r, plan, 0, n_blocks, out);
     } catch (...) {
+        if (r->event) give_request_event(p, r->event);
         p.requests.erase(slot);
         throw;
     }
@@ -644,6 +648,7 @@ void pool_release(Pool &p, uint64_t request)
     if (!p.placement_only) {
         DeviceScope dev(p.device);
         wait_call(p, rec.busy_call);
+        give_request_event(p, rec.event);
     }
     for (auto &a : rec.ranges) {
         p.regions[a.region].live.erase(a.base);

@@ -482,12 +482,6 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     // ordering with earlier work on the same requests from any stream:
     // retrieve after store (read after write), store after store/retrieve
     for (RequestRec *rec : touched) wait_for(gather ? rec->stored_call : rec->busy_call);
-    // The call's completion.  busy must cover every call still touching the
-    // request, not only this one: two retrieves of a request may run on
-    // different streams at once, and release, destroy and a later store wait on
-    // busy alone.  So when the previous one was on another stream, the caller's
-    // stream first waits for it (after this call's kernels, so only later work
-    // on the stream is held back), and the new one covers both.
     // one host-class kernel on the link at a time, in enqueue order: two of
     // them would only share its bandwidth and both end late
     auto take_link = [&] { wait_for(p.link_call[op]); };
@@ -502,15 +496,34 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             if (!gather) rec->stored_call = call;
         }
     };
+    // The call's completion.  busy must cover every call still touching the
+    // request, not only this one: two retrieves of a request may run on
+    // different streams at once, and release, destroy and a later store wait on
+    // busy alone.  So the caller's stream first waits for the previous one (after
+    // this call's kernels, so only later work on the stream is held back), and
+    // the new one covers both.  Its record in flight is made before the first
+    // launch, so that only the runtime can fail once something is enqueued.
+    struct Opened {
+        Pool &p;
+        hipEvent_t done = nullptr;   // null: not begun, or taken over
+        ~Opened()
+        {
+            if (done) cancel_call(p);
+        }
+    } opened{p};
+    auto begin = [&] {
+        if (!capturing) opened.done = begin_call(p, s, lent, touched.front()->event, !noalloc);
+    };
     auto finish = [&](bool on_link) {   // everything is enqueued: record it
         if (capturing) return;
-        for (RequestRec *rec : touched) wait_for(rec->busy_call);
-        const hipEvent_t done = begin_call(p, s, lent);
-        const hipError_t e = hipEventRecord(done, s);
-        if (e != hipSuccess) {
-            cancel_call(p);
-            check_hip(e, "hipEventRecord");
+        try {
+            for (RequestRec *rec : touched) wait_for(rec->busy_call);
+            check_hip(hipEventRecord(opened.done, s), "hipEventRecord");
+        } catch (...) {   // nothing will tell when the call is done, so it is done before this returns
+            (void)hipStreamSynchronize(s);
+            throw;
         }
+        opened.done = nullptr;
         touch(on_link);
     };
     const uint32_t chunks = 2 * (layer_end - layer_begin);
@@ -565,6 +578,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         std::copy(items[0].begin(), items[0].end(), list);
         std::copy(items[1].begin(), items[1].end(), list + items[0].size());
         if (host) take_link();
+        begin();
         check_hip(launch_call(f, gather, lh.grid, ls.grid, lh.flags, ls.flags, s), "kernel launch");
         finish(host);
         return;
@@ -600,8 +614,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         for (uint32_t h = 0; h < 2; ++h) {
             if (!(whole || h == half) || !sd->free_rec[h]) continue;
             check_hip(hipEventSynchronize(sd->free[h]), "hipEventSynchronize");
-            for (auto &f : p.flight)   // the event's next use is another call's
-                if (f.done == sd->free[h]) f.done = nullptr;
+            forget_event(p, sd->free[h]);   // its next use is another call's
         }
         lent = sd->free[half];
         host_list = static_cast<char *>(sd->host) + half * (kScratchBytes / 2);
@@ -619,6 +632,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     std::copy(items[1].begin(), items[1].end(), list + items[0].size());
     std::copy(file_items.begin(), file_items.end(), list + items[0].size() + items[1].size());
 
+    begin();
     check_hip(launch_list_copy(dev_base, host_list_dev, bytes, s), "kernel launch");
     slot = buffer;   // from here on the buffer is in use even if a launch fails
     auto took_scratch = [&] {   // after finish, which used free[half]
@@ -626,7 +640,10 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         sd->free_rec[half] = true;
         sd->next = half ^ 1u;
         if (whole) {
-            check_hip(hipEventRecord(sd->free[1], s), "hipEventRecord");
+            if (hipEventRecord(sd->free[1], s) != hipSuccess) {
+                clear_hip_error();
+                (void)hipStreamSynchronize(s);
+            }
             sd->free_rec[1] = true;
         }
     };
@@ -643,8 +660,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         try {
             finish(host);
             took_scratch();
-        } catch (...) {
-            (void)hipStreamSynchronize(s);   // nothing was recorded to wait for
+        } catch (...) {   // the call is done: finish saw to it
         }
         clear_hip_error();
     };

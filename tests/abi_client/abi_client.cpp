@@ -56,6 +56,30 @@ extern "C" hipError_t hipHostMalloc(void **ptr, size_t size, unsigned int flags)
     return real ? real(ptr, size, flags) : hipErrorNotInitialized;
 }
 
+// The same for events: how many were created, and creations and records made to fail.
+static unsigned g_events_created = 0;
+static bool g_fail_create = false, g_fail_next_record = false;
+
+extern "C" hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned flags)
+{
+    using Fn = hipError_t (*)(hipEvent_t *, unsigned);
+    static const Fn real = reinterpret_cast<Fn>(dlvsym(RTLD_NEXT, "hipEventCreateWithFlags", "hip_4.2"));
+    if (g_fail_create) return hipErrorOutOfMemory;
+    ++g_events_created;
+    return real ? real(e, flags) : hipErrorNotInitialized;
+}
+
+extern "C" hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
+{
+    using Fn = hipError_t (*)(hipEvent_t, hipStream_t);
+    static const Fn real = reinterpret_cast<Fn>(dlvsym(RTLD_NEXT, "hipEventRecord", "hip_4.2"));
+    if (g_fail_next_record) {
+        g_fail_next_record = false;
+        return hipErrorInvalidHandle;
+    }
+    return real ? real(e, s) : hipErrorNotInitialized;
+}
+
 int main(int argc, char **argv)
 {
     const bool exit_open = argc > 1 && std::strcmp(argv[1], "exit-open") == 0;
@@ -135,6 +159,43 @@ int main(int argc, char **argv)
     for (uint32_t i = 0; i < 2 * L; ++i) HIPTRY(hipMemset(dst[i], 0xA5, layer_bytes));
     TRY(kv_pool_retrieve_noalloc(pool, map.data(), n, dst_table.data(), slots, k_dst.data(), v_dst.data(), stream));
     HIPTRY(hipStreamSynchronize(stream));
+    if (check()) return 1;
+
+    // a hundred small calls behind a copy that holds the stream: by the allocation-free entry point, which
+    // creates no event, then by the ordinary one while none can be created
+    const size_t hold_bytes = 128u << 20;
+    void *hold_host = nullptr, *hold_dev = nullptr;
+    HIPTRY(hipHostMalloc(&hold_host, hold_bytes, hipHostMallocDefault));
+    HIPTRY(hipMalloc(&hold_dev, hold_bytes));
+    std::memset(hold_host, 0, hold_bytes);
+    TRY(kv_pool_set_launch(pool, KVP_CLASS_HOST, KVP_OP_RETRIEVE, 0, 0));
+    for (int ordinary = 0; ordinary < 2; ++ordinary) {
+        for (uint32_t i = 0; i < 2 * L; ++i) HIPTRY(hipMemset(dst[i], 0xA5, layer_bytes));
+        HIPTRY(hipDeviceSynchronize());
+        const unsigned before = g_events_created;
+        g_fail_create = ordinary;
+        HIPTRY(hipMemcpyAsync(hold_dev, hold_host, hold_bytes, hipMemcpyHostToDevice, stream));
+        for (int call = 0; call < 100; ++call) {
+            const uint32_t b = uint32_t(call) % n;
+            TRY((ordinary ? kv_pool_retrieve : kv_pool_retrieve_noalloc)(pool, &map[b], 1, &dst_table[b], slots,
+                                                                         k_dst.data(), v_dst.data(), stream));
+        }
+        if (g_events_created != before) ++bad;
+        g_fail_create = false;
+        HIPTRY(hipStreamSynchronize(stream));
+        if (check()) return 1;
+    }
+    HIPTRY(hipFree(hold_dev));
+    HIPTRY(hipHostFree(hold_host));
+
+    // a call whose completion cannot be recorded: an error, and nothing of it is left running
+    for (uint32_t i = 0; i < 2 * L; ++i) HIPTRY(hipMemset(dst[i], 0xA5, layer_bytes));
+    HIPTRY(hipDeviceSynchronize());
+    g_fail_next_record = true;
+    if (kv_pool_retrieve(pool, map.data(), n, dst_table.data(), slots, k_dst.data(), v_dst.data(), stream) !=
+            KVP_ERR_HIP ||
+        hipStreamQuery(stream) != hipSuccess || hipGetLastError() != hipSuccess)
+        ++bad;
     if (check()) return 1;
 
     // the same request through the copy engines: ring slots of one block, two layer ranges

@@ -693,7 +693,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             }
         };
         const bool staging = !items[KVP_CLASS_STAGING].empty();
-        if (one_launch && file_batches.empty()) {
+        if (one_launch) {
             CallArgs f = {};
             f.a = args[KVP_CLASS_HOST];
             f.a.n_items += args[KVP_CLASS_STAGING].n_items;

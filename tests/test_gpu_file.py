@@ -331,3 +331,43 @@ def test_read_error_mid_call_then_the_pool_still_works(tmp_path):
         for b in range(n):
             assert torch.equal(dst[:, :, dst_tab[b]], src[:, :, src_tab[b]]), "block %d after the error" % b
 
+
+
+def test_the_other_classes_run_side_by_side_with_files_in_the_call(tmp_path):
+    """One file block beside 400 host and 20,000 staging blocks, each about 2 ms of the link and of HBM:
+    one call of all three takes clearly less than its host and its staging blocks one after the other."""
+    spec = K.KVSpec(4, 8, 128, 16, 2, 0)
+    per = [400, 20000, 1]
+    n = sum(per)
+    kinds = ("host", "staging", "file")
+    room = [-(-(c + 1) * spec.block_bytes // 4096) * 4096 for c in per]
+    regions = [K.Region(k, size, path=str(tmp_path / "region.bin") if k == "file" else None)
+               for k, size in zip(kinds, room)]
+    with K.KVPool(regions, per, spec) as pool:
+        m = pool.place(1, n)
+        assert [int((m["region"] == r).sum()) for r in range(3)] == per
+        src = torch.randint(-2**15, 2**15, (4, 2, n, 8, 16, 128), dtype=torch.int16, device="cuda")
+        dst = torch.zeros_like(src)
+        (sk, sv), (dk, dv) = [[[c[i].data_ptr() for c in t] for i in (0, 1)] for t in (src, dst)]
+        table = np.random.default_rng(5).permutation(n).astype(np.int32)
+        stream = torch.cuda.current_stream().cuda_stream
+        pool.store(m, np.arange(n, dtype=np.int32), n, sk, sv, stream)
+
+        def ms(wanted):
+            part = m.copy()
+            part["region"][~np.isin(m["region"], wanted)] = K.ABSENT
+            best = float("inf")
+            for _ in range(6):
+                torch.cuda.synchronize()
+                e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                e[0].record()
+                pool.retrieve(part, table, n, dk, dv, stream)
+                e[1].record()
+                torch.cuda.synchronize()
+                best = min(best, e[0].elapsed_time(e[1]))
+            return best
+
+        host, staging, whole = ms([0]), ms([1]), ms([0, 1, 2])
+        say("host %.2f ms, staging %.2f ms, with a file block %.2f ms" % (host, staging, whole))
+        assert whole < 0.8 * (host + staging)
+        assert bool((dst[:, :, torch.from_numpy(table.astype(np.int64)).cuda()] == src).all())

@@ -243,12 +243,16 @@ int kv_pool_store(kvp_pool *pool, const kvp_loc *map, uint32_t n_blocks,
 /*
  * Retrieve (Sec. 4.3, "KV Retrieval"): group the present entries by region
  * type, then read the host regions (zero-copy) and the staging regions (HBM
- * gather) in parallel, both by one kernel on `stream`.  A timed call, and one
- * of a token-major pool whose chunks exceed 20 KiB and whose list is too large
- * for a small call (kv_pool_set_launch), takes two kernels: the HBM one on the
- * pool's internal stream, forked from `stream` and joined back into it, or, for
- * under 32 MiB of staging-region bytes, on `stream` ahead of the host-region
- * one, since forking costs more.  Every chunk
+ * gather) in parallel, both by one kernel on `stream`.  Two kernels are taken
+ * by a timed call, by one of a token-major pool whose chunks exceed 20 KiB and
+ * whose list is too large for a small call (kv_pool_set_launch), and, with 32
+ * MiB of staging-region bytes or more, by one that finds the host link taken by
+ * another stream's call or whose staging regions take longer than its host
+ * regions, but less than twice as long (the link is handed on when it is free;
+ * a call that needs it for less than half of its time shares it): the HBM one
+ * on the pool's internal stream, forked from `stream` and joined back into it,
+ * or, for under 32 MiB of staging-region bytes, on `stream` ahead of the
+ * host-region one, since forking costs more.  Every chunk
  * lands in slot dst_block_table[b] of layer l's K or V buffer in the engine
  * layout.
  * Absent entries are skipped and every slot not named by a present entry is
@@ -454,7 +458,8 @@ int kv_pool_set_bandwidths(kvp_pool *pool, const uint64_t *bandwidths);
  * uses fewer host workgroups, down to a third (the link's writes slow the HBM
  * kernel beside them).  With the default host-class
  * retrieve grid, a retrieve enqueued while a host-class store kernel of this
- * pool has not finished takes 48 workgroups: with traffic both ways the
+ * pool has not finished (one that holds the link) takes 48 workgroups: with
+ * traffic both ways the
  * link's reads need more in flight (measured on MI355X, a 128K-token
  * LLaMA-shaped store and retrieve at once: 264.6 instead of 320 ms), while
  * alone, or beside HBM-bound kernels, 12 do as well or better.  An explicit

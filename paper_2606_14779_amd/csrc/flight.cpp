@@ -100,7 +100,7 @@ hipEvent_t begin_call(Pool &p, hipStream_t s, hipEvent_t lent, hipEvent_t own, b
         } catch (const Error &) {   // the request's event will do
         }
     }
-    if (!lent && p.idle.empty()) lent = own;
+    if (!lent && p.idle.empty() && !(lent = own)) return nullptr;
     p.flight.push_back(FlightRec{lent ? lent : p.idle.back(), s, !lent});
     if (!lent) p.idle.pop_back();
     return p.flight.back().done;

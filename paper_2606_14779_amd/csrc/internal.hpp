@@ -361,8 +361,9 @@ struct Pool {
     uint64_t flight_first = 1;
     std::vector<hipEvent_t> idle;       // events for later calls, with room for every one of the pool
     size_t events = 0;                  // made so far: idle, of calls in flight, of requests
-    // host link, per direction [op]: the last call with a host-class kernel; the
-    // next one (any stream) waits for it, so calls take the link in turn
+    // host link, per direction [op]: the last call that holds it, or the record of
+    // that call's host-class part; the next one (any stream) waits for it, so calls
+    // take the link in turn
     uint64_t link_call[2] = {0, 0};
     std::vector<Slot> ring;
     uint32_t ring_next = 0;
@@ -408,7 +409,8 @@ void land_done_calls(Pool &p);                              // notice finished c
 // pool's idle events, made if there is none and may_create; else `own`, the event
 // of a request of the call, which the call may always use: it records it only
 // after its stream waited for that request's earlier calls.  An event recorded
-// again makes earlier calls that hold it look done later, never sooner.
+// again makes earlier calls that hold it look done later, never sooner.  No event
+// and no `own`: null, and no record is made.
 hipEvent_t begin_call(Pool &p, hipStream_t s, hipEvent_t lent, hipEvent_t own, bool may_create);
 void cancel_call(Pool &p) noexcept;                         // nothing of it was enqueued, or all of it is done
 uint64_t last_call(const Pool &p);

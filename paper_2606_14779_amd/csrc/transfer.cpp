@@ -39,19 +39,20 @@ constexpr uint64_t kForkMinBytes = 32ull << 20;
 // work, loses with more).
 constexpr uint32_t kDuplexReadGrid = 48;
 constexpr uint64_t kMergeLdsMax = 20 * 1024;   // 160 KiB of LDS hold 8 workgroups of this size
+constexpr uint64_t kHbmPerLink = 54;           // bytes that HBM moves while the link moves one
 
 // Host-class store workgroups beside a staging-class store that takes longer.
 // The link's posted writes fill the write path that the HBM kernel shares, and
 // the more of them wait, the slower it gets, so the host class takes only the
 // workgroups with which it ends in about two thirds of the staging class's
-// time (HBM moves 54 bytes for one over the link), a third of its own choice
+// time, a third of its own choice
 // at least.  4096 Qwen3-shaped blocks on measured weights, 20 of them over the
 // link (27 % of the staging class's time alone), took 2400 us with 12 host
 // workgroups, 2193 with 8, 2166 with 3 to 6, 2177 with 2 and 2700 with 1.  A
 // retrieve's reads don't have this effect (2183-2208 us with 12, 2182 with 6).
 uint32_t throttled_store_grid(uint32_t grid, uint64_t host_bytes, uint64_t staging_bytes)
 {
-    const double share = 54.0 * static_cast<double>(host_bytes) / static_cast<double>(staging_bytes);
+    const double share = static_cast<double>(kHbmPerLink * host_bytes) / static_cast<double>(staging_bytes);
     const uint32_t least = (grid + 2) / 3;
     return std::min(grid, std::max(least, static_cast<uint32_t>(1.5 * share * grid) + 1));
 }
@@ -487,10 +488,11 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     auto take_link = [&] { wait_for(p.link_call[op]); };
     Slot *slot = nullptr;        // the call's work-list buffer, once it is in use
     hipEvent_t lent = nullptr;   // the allocation-free call's event
+    uint64_t link_part = 0;      // record of the host-class kernel alone, once it is recorded
     auto touch = [&](bool on_link) {   // the call is last_call()
         const uint64_t call = last_call(p);
         if (slot) slot->call = call;
-        if (on_link) p.link_call[op] = call;
+        if (on_link) p.link_call[op] = link_part ? link_part : call;
         for (RequestRec *rec : touched) {
             rec->busy_call = call;
             if (!gather) rec->stored_call = call;
@@ -505,14 +507,24 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     // launch, so that only the runtime can fail once something is enqueued.
     struct Opened {
         Pool &p;
-        hipEvent_t done = nullptr;   // null: not begun, or taken over
+        hipEvent_t done = nullptr, link_done = nullptr;
+        uint32_t records = 0;   // to be taken back
         ~Opened()
         {
-            if (done) cancel_call(p);
+            for (; records; --records) cancel_call(p);
         }
     } opened{p};
-    auto begin = [&] {
-        if (!capturing) opened.done = begin_call(p, s, lent, touched.front()->event, !noalloc);
+    auto begin = [&](bool with_link_part = false) {
+        if (capturing) return;
+        if (with_link_part) opened.link_done = begin_call(p, s, nullptr, nullptr, !noalloc);
+        opened.records += opened.link_done != nullptr;
+        opened.done = begin_call(p, s, lent, touched.front()->event, !noalloc);
+        ++opened.records;
+    };
+    auto link_part_done = [&] {   // the host-class kernel is enqueued, other parts of the call may outlast it
+        if (!opened.link_done) return;
+        check_hip(hipEventRecord(opened.link_done, s), "hipEventRecord");
+        link_part = last_call(p) - 1;
     };
     auto finish = [&](bool on_link) {   // everything is enqueued: record it
         if (capturing) return;
@@ -523,7 +535,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             (void)hipStreamSynchronize(s);
             throw;
         }
-        opened.done = nullptr;
+        opened.records = 0;
         touch(on_link);
     };
     const uint32_t chunks = 2 * (layer_end - layer_begin);
@@ -546,16 +558,32 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     const LaunchCfg &ls = p.launch[KVP_CLASS_STAGING][op];
     LaunchCfg lh = p.launch[KVP_CLASS_HOST][op];
     const bool host = !items[KVP_CLASS_HOST].empty();
-    // One launch for both classes, unless each is timed or the host class's LDS
+    // One launch for both classes, unless each is timed, the host class's LDS
     // would hold the HBM kernel's workgroups back (their wavefronts fill a CU
-    // with 8 workgroups).  In two launches the internal stream takes the staging
+    // with 8 workgroups), or the link has to be waited for or handed on while the
+    // HBM kernel runs.  In two launches the internal stream takes the staging
     // class, for enough of its bytes.
     const bool lds = p.spec.pool_layout == 1 && (lh.flags & KVP_LAUNCH_LDS) != 0;
     const bool both = host && !items[KVP_CLASS_STAGING].empty();
-    const bool one_launch =
-        batches.empty() && (noalloc || !p.timing) && !(both && lds && p.chunk_bytes > kMergeLdsMax);
-    const bool large = batches.empty() && items[KVP_CLASS_STAGING].size() * width >= kForkMinBytes;
+    const uint64_t staging_bytes = items[KVP_CLASS_STAGING].size() * width;
+    const uint64_t link_bytes = kHbmPerLink * items[KVP_CLASS_HOST].size() * width;   // as HBM bytes of the same time
+    const bool large = batches.empty() && staging_bytes >= kForkMinBytes;
+    // The one launch ends with its longer class.  If that is the host class, the
+    // end hands the link on in time.  If HBM takes more than twice as long, the
+    // call does not hold the link at all: whoever shares it has it back before
+    // this call ends, and sooner than by waiting for the end.  In between, the host
+    // class has a kernel and a record of its own.
+    const bool outlasts = both && large && staging_bytes > link_bytes;
+    const bool shares_link = outlasts && staging_bytes > 2 * link_bytes;
+    auto link_taken = [&] {   // by an unfinished call of another stream
+        const FlightRec *f = in_flight(p, p.link_call[op]);
+        return f && f->stream != s && hipPeekAtLastError() == hipSuccess && !event_done(f->done);
+    };
+    const bool one_launch = batches.empty() && (noalloc || !p.timing) &&
+                            !(both && lds && p.chunk_bytes > kMergeLdsMax) && !(outlasts && !shares_link) &&
+                            !(both && large && !capturing && link_taken());
     const bool fork_staging = large && host && !one_launch;
+    const bool holds_link = host && batches.empty() && !(one_launch && shares_link);
     const FlightRec *storing = in_flight(p, p.link_call[KVP_OP_STORE]);
     // a store's host-class kernel not yet finished: the link carries traffic both ways
     if (gather && host && lh.default_grid && storing && lh.grid < kDuplexReadGrid && !capturing &&
@@ -632,7 +660,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     std::copy(items[1].begin(), items[1].end(), list + items[0].size());
     std::copy(file_items.begin(), file_items.end(), list + items[0].size() + items[1].size());
 
-    begin();
+    begin(holds_link && (fork_staging || !file_batches.empty()));
     check_hip(launch_list_copy(dev_base, host_list_dev, bytes, s), "kernel launch");
     slot = buffer;   // from here on the buffer is in use even if a launch fails
     auto took_scratch = [&] {   // after finish, which used free[half]
@@ -658,7 +686,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         (void)hipEventRecord(p.stage_done, p.s_stage);
         (void)hipStreamWaitEvent(s, p.stage_done, 0);
         try {
-            finish(host);
+            finish(holds_link);
             took_scratch();
         } catch (...) {   // the call is done: finish saw to it
         }
@@ -704,6 +732,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             check_hip(both ? launch_call(f, gather, lh.grid, ls.grid, lh.flags, ls.flags, s)
                            : launch_chunk_copy(args[c], c, gather, lc.grid, lc.flags, s),
                       "kernel launch");
+            link_part_done();
         } else if (batches.empty()) {
             if (fork_staging) {
                 check_hip(hipStreamWaitEvent(p.s_stage, p.fork, 0), "hipStreamWaitEvent");
@@ -715,6 +744,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
             if (host) {
                 take_link();
                 launch(KVP_CLASS_HOST, s);
+                link_part_done();
             }
             if (fork_staging) check_hip(hipStreamWaitEvent(s, p.stage_done, 0), "hipStreamWaitEvent");
         } else {
@@ -803,7 +833,7 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         settle();
         throw;
     }
-    finish(host && batches.empty());
+    finish(holds_link);
     took_scratch();
 }
 

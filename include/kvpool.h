@@ -245,7 +245,10 @@ int kv_pool_store(kvp_pool *pool, const kvp_loc *map, uint32_t n_blocks,
  * type, then read the host regions (zero-copy) and the staging regions (HBM
  * gather) in parallel, both by one kernel on `stream`.  Two kernels are taken
  * by a timed call, by one of a token-major pool whose chunks exceed 20 KiB and
- * whose list is too large for a small call (kv_pool_set_launch), and, with 32
+ * whose list is too large for a small call (kv_pool_set_launch), by one with
+ * flags that the one kernel does not have (KVP_LAUNCH_XCD, _CHUNK_MAJOR or _TILE
+ * on the host class; no KVP_LAUNCH_NT_STORE or, for pool_layout 0, no
+ * KVP_LAUNCH_NT_LOAD on the staging class; small calls go without), and, with 32
  * MiB of staging-region bytes or more, by one that finds the host link taken by
  * another stream's call or whose staging regions take longer than its host
  * regions, but less than twice as long (the link is handed on when it is free;

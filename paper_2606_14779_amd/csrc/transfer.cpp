@@ -560,11 +560,15 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     const bool host = !items[KVP_CLASS_HOST].empty();
     // One launch for both classes, unless each is timed, the host class's LDS
     // would hold the HBM kernel's workgroups back (their wavefronts fill a CU
-    // with 8 workgroups), or the link has to be waited for or handed on while the
-    // HBM kernel runs.  In two launches the internal stream takes the staging
-    // class, for enough of its bytes.
+    // with 8 workgroups), the flags ask for what the one launch does not have, or
+    // the link has to be waited for or handed on while the HBM kernel runs.  In
+    // two launches the internal stream takes the staging class, for enough of its
+    // bytes.
     const bool lds = p.spec.pool_layout == 1 && (lh.flags & KVP_LAUNCH_LDS) != 0;
     const bool both = host && !items[KVP_CLASS_STAGING].empty();
+    const uint32_t staging_hints = KVP_LAUNCH_NT_STORE | (p.spec.pool_layout == 0 ? KVP_LAUNCH_NT_LOAD : 0u);
+    const bool own_forms = (lh.flags & (KVP_LAUNCH_XCD | KVP_LAUNCH_CHUNK_MAJOR | KVP_LAUNCH_TILE)) != 0 ||
+                           (ls.flags & staging_hints) != staging_hints;
     const uint64_t staging_bytes = items[KVP_CLASS_STAGING].size() * width;
     const uint64_t link_bytes = kHbmPerLink * items[KVP_CLASS_HOST].size() * width;   // as HBM bytes of the same time
     const bool large = batches.empty() && staging_bytes >= kForkMinBytes;
@@ -580,8 +584,8 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         return f && f->stream != s && hipPeekAtLastError() == hipSuccess && !event_done(f->done);
     };
     const bool one_launch = batches.empty() && (noalloc || !p.timing) &&
-                            !(both && lds && p.chunk_bytes > kMergeLdsMax) && !(outlasts && !shares_link) &&
-                            !(both && large && !capturing && link_taken());
+                            !(both && lds && p.chunk_bytes > kMergeLdsMax) && !(both && own_forms) &&
+                            !(outlasts && !shares_link) && !(both && large && !capturing && link_taken());
     const bool fork_staging = large && host && !one_launch;
     const bool holds_link = host && batches.empty() && !(one_launch && shares_link);
     const FlightRec *storing = in_flight(p, p.link_call[KVP_OP_STORE]);

@@ -847,7 +847,7 @@ def latency(args):
     regions) for n = 1 ... 1024, one call at a time with a host synchronisation after each.  This is
     the fixed cost per call that a fetch of a few blocks sees.  Calls with a small work list run as one
     launch with the list in the kernel arguments; --upload times them the way larger calls run (work
-    list uploaded, one launch per region class)."""
+    list uploaded first)."""
     import torch
 
     from kvgen import workloads
@@ -1050,7 +1050,7 @@ def main():
     ap.add_argument("--latency", action="store_true",
                     help="instead of the bench line, time single retrieves of the first 1 ... 1024 blocks")
     ap.add_argument("--upload", action="store_true",
-                    help="with --latency: no small-call launch (upload the work list, one launch per class)")
+                    help="with --latency: no small-call launch (upload the work list first)")
     ap.add_argument("--flush", action="store_true",
                     help="overwrite 1 GiB before each timed step; ms_per_step is then the median event span")
     ap.add_argument("--stand-in", choices=["gemm", "copy"], default="gemm",

@@ -17,7 +17,7 @@
 // that is still running.
 
 #include <algorithm>
-
+#include <cmath>
 #include <unordered_map>
 
 #include "internal.hpp"
@@ -45,16 +45,21 @@ constexpr uint64_t kHbmPerLink = 54;           // bytes that HBM moves while the
 // The link's posted writes fill the write path that the HBM kernel shares, and
 // the more of them wait, the slower it gets, so the host class takes only the
 // workgroups with which it ends in about two thirds of the staging class's
-// time, a third of its own choice
-// at least.  4096 Qwen3-shaped blocks on measured weights, 20 of them over the
-// link (27 % of the staging class's time alone), took 2400 us with 12 host
-// workgroups, 2193 with 8, 2166 with 3 to 6, 2177 with 2 and 2700 with 1.  A
-// retrieve's reads don't have this effect (2183-2208 us with 12, 2182 with 6).
+// time, a third of its own choice at least.  4096 Qwen3-shaped blocks on
+// measured weights, 20 of them over the link (27 % of the staging class's time
+// alone), took 2400 us with 12 host workgroups, 2193 with 8, 2166 with 3 to 6,
+// 2177 with 2 and 2700 with 1.  Over three shapes, both pool layouts and link
+// times of 2 to 95 % of HBM's (2 GB in HBM each) the rule is nowhere over 1 %
+// slower than all workgroups, and gains 1 to 14 % up to 45 % (27 %: 689 against 737 us
+// head-major, 704 against 751 token-major).  It is not the best choice above that:
+// half of the workgroups take 655 and 692 us at 45 and 60 %, the rule 753 and
+// 840.  A retrieve's reads don't have this effect (2183-2208 us with 12, 2182
+// with 6).
 uint32_t throttled_store_grid(uint32_t grid, uint64_t host_bytes, uint64_t staging_bytes)
 {
     const double share = static_cast<double>(kHbmPerLink * host_bytes) / static_cast<double>(staging_bytes);
     const uint32_t least = (grid + 2) / 3;
-    return std::min(grid, std::max(least, static_cast<uint32_t>(1.5 * share * grid) + 1));
+    return std::max(least, static_cast<uint32_t>(std::min<double>(grid, std::floor(1.5 * share * grid) + 1)));
 }
 
 // The live allocation holding the block at map entry e, or an error.
@@ -313,8 +318,9 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         if (!k || !v || (k & 15) || (v & 15))
             fail(KVP_ERR_INVALID, "layer " + std::to_string(l) + ": null or unaligned cache pointer");
     }
-    // a kernel's units (blocks x 2L chunks x at most 2 parts) and its workgroup stride (at most 2^20)
-    // are summed in 32 bits: at most 2^31 units keeps that sum from wrapping
+    // A link kernel's units (blocks x 2L chunks x at most 2 parts) and its workgroup stride (at most 2^20)
+    // are summed in 32 bits: at most 2^31 units keeps that sum from wrapping.  The HBM body's units are
+    // smaller; its launch makes them larger where there would be over 2^31, beside a stride of at most 2^23.
     if (static_cast<uint64_t>(n_blocks) * 4 * L > (1ull << 31)) fail(KVP_ERR_INVALID, "request too large");
 
     std::lock_guard<std::mutex> lock(p.mu);

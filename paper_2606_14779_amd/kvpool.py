@@ -31,7 +31,7 @@ CLASS_HOST, CLASS_STAGING = 0, 1
 OP_RETRIEVE, OP_STORE = 0, 1
 LAUNCH_NT_LOAD, LAUNCH_NT_STORE, LAUNCH_LDS, LAUNCH_SPLIT2, LAUNCH_XCD, LAUNCH_SDMA = 1, 2, 4, 8, 16, 32
 LAUNCH_CHUNK_MAJOR = 64
-LAUNCH_UPLOAD = 128          # no small-call launch: upload the work list, one launch per class
+LAUNCH_UPLOAD = 128          # no small-call launch: upload the work list
 LAUNCH_TILE = 256            # workgroup-owned tiles of 8 work items x 1 chunk
 MEASURE_SHARED_LINK = 1
 MEASURE_SHARED_HBM = 4       # staging regions share the one GPU's HBM: their rate divided by their count

@@ -148,7 +148,7 @@ int main(int argc, char **argv)
     };
     if (check()) return 1;   // store and retrieve fit the small-call launch (work list in the kernel arguments)
 
-    // the same request through the upload path: work list uploaded, one launch per region class
+    // the same request through the upload path: work list uploaded ahead of the launch
     for (uint32_t i = 0; i < 2 * L; ++i) HIPTRY(hipMemset(dst[i], 0xA5, layer_bytes));
     TRY(kv_pool_set_launch(pool, KVP_CLASS_HOST, KVP_OP_RETRIEVE, 0, KVP_LAUNCH_UPLOAD));
     TRY(kv_pool_retrieve(pool, map.data(), n, dst_table.data(), slots, k_dst.data(), v_dst.data(), stream));

@@ -3,7 +3,7 @@ arguments (384 words: one engine pointer per moved chunk, two words per
 present block) runs both region classes in one launch, with no upload.
 
 Every case runs the same seeded inputs through that launch and through the
-upload path (KVP_LAUNCH_UPLOAD: work list uploaded, one launch per class),
+upload path (KVP_LAUNCH_UPLOAD: work list uploaded, then the same launch),
 and checks each against the oracle bit for bit.  Sizes sit on both sides of
 the inline capacity: 160 blocks for the 32-layer LLaMA shape, 168 for the
 24-layer GPT-OSS shape, 191 when one layer of a 32-layer cache moves.

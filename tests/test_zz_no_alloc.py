@@ -104,6 +104,49 @@ def test_noalloc_back_to_back_on_two_streams():
         run.close()
 
 
+def test_noalloc_lists_share_the_array():
+    """Lists too large for the kernel arguments, of two pools on two streams, back to back behind a copy that
+    holds the first stream up: lists that fit a half, in turn, and lists that take both halves between
+    them.  Each call has a destination of its own, equal to its source blocks and untouched elsewhere."""
+    spec = K.KVSpec(1, 1, 8, 1, 2, 0)                       # one-layer blocks of 32 bytes
+    n = 60000
+    calls = [(0, 0, 300), (1, 1, 20000), (0, 0, 30000), (1, 1, 250), (0, 1, 40000), (1, 0, 60000), (1, 1, 200),
+             (0, 0, 32000), (0, 1, 33000), (0, 0, 400), (1, 0, 500), (0, 1, 600), (1, 0, 50000)]   # pool, stream, blocks
+    say("case noalloc array shared")
+    rng = np.random.default_rng(11)
+    pools = [K.KVPool([K.Region("staging", n * 32), K.Region("host", n * 32, -1)], [1, 1], spec, 0) for _ in range(2)]
+    try:
+        src = torch.randint(-32768, 32767, (2, 2, n, 8), dtype=torch.int16, device="cuda")   # pool, K/V, slot
+        cur = torch.cuda.current_stream()
+        maps = []
+        for p, t in zip(pools, src):
+            maps.append(p.place(1, n))
+            p.store(maps[-1], np.arange(n, dtype=np.int32), n, [t[0].data_ptr()], [t[1].data_ptr()], cur.cuda_stream)
+        dst = torch.zeros((len(calls), 2, n, 8), dtype=torch.int16, device="cuda")
+        held = torch.empty(128 << 20, dtype=torch.uint8, pin_memory=True)
+        sink = torch.empty(128 << 20, dtype=torch.uint8, device="cuda")
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        picks = [np.sort(rng.permutation(n)[:count]) for _, _, count in calls]
+        tables = [rng.permutation(n)[:count].astype(np.int32) for _, _, count in calls]
+        for s in streams:
+            s.wait_stream(cur)
+        with torch.cuda.stream(streams[0]):
+            sink.copy_(held, non_blocking=True)
+        for (p, s, _), pick, table, d in zip(calls, picks, tables, dst):
+            pools[p].retrieve_noalloc(maps[p][pick], table, n, [d[0].data_ptr()], [d[1].data_ptr()],
+                                      streams[s].cuda_stream)
+        torch.cuda.synchronize()
+        for (p, _, count), pick, table, d in zip(calls, picks, tables, dst):
+            at, of = (torch.from_numpy(x.astype(np.int64)).cuda() for x in (table, pick))
+            assert torch.equal(d[:, at], src[p][:, of]), "call of %d blocks differs" % count
+            d[:, at] = 0
+            assert not bool(d.any()), "call of %d blocks wrote elsewhere" % count
+    finally:
+        torch.cuda.synchronize()
+        for p in pools:
+            p.close()
+
+
 def test_noalloc_ignores_copy_engine_setting():
     """With the copy-engine transport set for the host class, the allocation-free call still runs
     the zero-copy kernel and returns the same bytes as kv_pool_retrieve."""

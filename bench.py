@@ -52,6 +52,13 @@ HBM_PROBE_GRIDS = (2048, 8192, 32768, 65536, 262144)   # grids of the 4 GiB HBM 
 SAME_BYTES_GRIDS = (16384, 131072, 1048576)   # grids of the same-bytes copy probe: none of the 4 GiB sweep's
 
 
+def hbm_probe_forms(K, grids, flags):
+    """(grid, flags) of every contiguous copy tried: these grids and flags, and one vector per lane and one
+    tile per workgroup (grid 0), the form of the library's own HBM kernels."""
+    return [(g, f) for g in grids for f in flags] + [
+        (0, K.LAUNCH_TILE | f) for f in (0, K.LAUNCH_NT_LOAD, K.LAUNCH_NT_LOAD | K.LAUNCH_NT_STORE)]
+
+
 def probes(torch, K, run, nbytes, same_bytes=0):
     """Copy peaks in GB/s (1e9 B/s of copied bytes), measured on this GPU in this process.
 
@@ -70,13 +77,13 @@ def probes(torch, K, run, nbytes, same_bytes=0):
         b = torch.empty_like(a)
         a.fill_(1)
         best, bgrid, bflags = 0.0, 0, 0
-        for grid in SAME_BYTES_GRIDS:
-            for fl in (K.LAUNCH_SPLIT2, K.LAUNCH_SPLIT2 | K.LAUNCH_NT_LOAD,
-                       K.LAUNCH_SPLIT2 | K.LAUNCH_NT_LOAD | K.LAUNCH_NT_STORE):
-                ms = min(_events_ms(torch, lambda: K.probe_copy_kernel(b.data_ptr(), a.data_ptr(), n, grid, fl,
-                                                                       cur.cuda_stream)))
-                if n / ms / 1e6 > best:
-                    best, bgrid, bflags = n / ms / 1e6, grid, fl
+        for grid, fl in hbm_probe_forms(K, SAME_BYTES_GRIDS, (
+                K.LAUNCH_SPLIT2, K.LAUNCH_SPLIT2 | K.LAUNCH_NT_LOAD,
+                K.LAUNCH_SPLIT2 | K.LAUNCH_NT_LOAD | K.LAUNCH_NT_STORE)):
+            ms = min(_events_ms(torch, lambda: K.probe_copy_kernel(b.data_ptr(), a.data_ptr(), n, grid, fl,
+                                                                   cur.cuda_stream)))
+            if n / ms / 1e6 > best:
+                best, bgrid, bflags = n / ms / 1e6, grid, fl
         res["hbm_copy_same_bytes"] = {"bytes": n, "gbps": round(best, 1), "grid": bgrid, "flags": bflags}
         del a, b
         torch.cuda.empty_cache()
@@ -84,14 +91,14 @@ def probes(torch, K, run, nbytes, same_bytes=0):
     b = torch.empty_like(a)
     a.fill_(1)
     best_k, best_grid, best_flags = 0.0, 0, 0
-    for grid in HBM_PROBE_GRIDS:
-        for fl in (0, K.LAUNCH_NT_LOAD, K.LAUNCH_SPLIT2, K.LAUNCH_SPLIT2 | K.LAUNCH_NT_LOAD,
-                   K.LAUNCH_SPLIT2 | K.LAUNCH_NT_LOAD | K.LAUNCH_NT_STORE):
-            ms = min(_events_ms(torch, lambda: K.probe_copy_kernel(b.data_ptr(), a.data_ptr(), nbytes, grid, fl,
-                                                                   cur.cuda_stream)))
-            gbps = nbytes / ms / 1e6
-            if gbps > best_k:
-                best_k, best_grid, best_flags = gbps, grid, fl
+    for grid, fl in hbm_probe_forms(K, HBM_PROBE_GRIDS, (
+            0, K.LAUNCH_NT_LOAD, K.LAUNCH_SPLIT2, K.LAUNCH_SPLIT2 | K.LAUNCH_NT_LOAD,
+            K.LAUNCH_SPLIT2 | K.LAUNCH_NT_LOAD | K.LAUNCH_NT_STORE)):
+        ms = min(_events_ms(torch, lambda: K.probe_copy_kernel(b.data_ptr(), a.data_ptr(), nbytes, grid, fl,
+                                                               cur.cuda_stream)))
+        gbps = nbytes / ms / 1e6
+        if gbps > best_k:
+            best_k, best_grid, best_flags = gbps, grid, fl
     ms = min(_events_ms(torch, lambda: K.probe_memcpy(b.data_ptr(), a.data_ptr(), nbytes, cur.cuda_stream)))
     res["hbm_copy_kernel_gbps"] = round(best_k, 1)
     res["hbm_copy_kernel_grid"] = best_grid
@@ -1197,13 +1204,11 @@ def main():
         step()
     torch.cuda.synchronize()
 
-    # timed region: K retrieves back to back; the library records HIP events
-    # around each kernel on the stream it runs on, summarised afterwards
+    # timed region: K retrieves back to back, as a program makes them
     log("warm-up done; timing %d steps" % args.steps)
     # --flush: before each step, overwrite 1 GiB (more than the 256 MiB Infinity Cache plus the L2s)
     # on the same stream, so every step starts cold; the per-step event span then excludes the flush
     flush = torch.empty(1 << 29, dtype=torch.int16, device="cuda") if args.flush else None
-    run.pool.set_timing(True)
     spans, enqueue_ms = [], []
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -1219,6 +1224,13 @@ def main():
         spans.append((s, e))
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
+    # the kernels' own times, from as many further retrieves: the library then records HIP events around
+    # each kernel, which takes a kernel of its own for each class
+    run.pool.set_timing(True)
+    for i in range(args.steps):
+        if flush is not None:
+            flush.fill_(i)
+        step()
     summ = run.pool.timing_summary()
     run.pool.set_timing(False)
     span_ms = [s.elapsed_time(e) for s, e in spans]
@@ -1395,9 +1407,9 @@ def main():
     if cpu:
         log("cpu baseline done")
 
-    # copy form in the kernels' names (template argument 2): 0 plain chunks; 2 token-major chunks
-    # through LDS, the library's default for every token-major kernel these figures cover
-    kform = 0 if wl.layout == 0 else 2
+    # copy form in the host-class kernels' names (template argument 2): 0 plain chunks; token-major chunks
+    # through LDS (2) in a retrieve, directly (1) in a store.  The staging-class kernels name the layout.
+    kform, kform_store = (0, 0) if wl.layout == 0 else (2, 1)
     token_major = "false" if wl.layout == 0 else "true"
     # the dominant kernel: the class whose kernel takes longer per step
     dominant_host = bool(host_blocks) and (not stage_blocks or (host_avg or 0.0) >= (stage_avg or 0.0))
@@ -1466,7 +1478,7 @@ def main():
     store_roof = None
     if store and host_blocks:
         a = host_bytes / (store["host_kernel_ms_avg"] / 1e3) / 1e9
-        trw = pmc_traffic(wl.name, "host_region_copy<false, %d," % kform)
+        trw = pmc_traffic(wl.name, "host_region_copy<false, %d," % kform_store)
         store_roof = {"bound": "pcie", "kernel": "host_region_copy<false,...> (zero-copy store to pinned host regions)",
                       "achieved": round(a, 2), "peak": PCIE5_X16_GBPS, "unit": "GB/s",
                       "frac": round(a / PCIE5_X16_GBPS, 4),

@@ -571,7 +571,8 @@ int kv_pool_timing_summary(kvp_pool *pool, kvp_timing_summary *out);
 
 /* Streaming copy kernel: bytes from src to dst (device-visible addresses,
  * 16-byte aligned, bytes a multiple of 16), `grid` workgroups of 256
- * threads (0 = default), KVP_LAUNCH_NT_* and KVP_LAUNCH_SPLIT2 flags, on
+ * threads (0 = default), KVP_LAUNCH_NT_*, KVP_LAUNCH_SPLIT2 and
+ * KVP_LAUNCH_TILE (256 x 1-vector tiles, by default one per workgroup) flags, on
  * `stream` of the current device.  Errors: INVALID, HIP. */
 int kv_probe_copy_kernel(void *dst, const void *src, uint64_t bytes, uint32_t grid,
                          uint32_t flags, void *stream);

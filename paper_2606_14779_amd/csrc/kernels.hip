@@ -485,7 +485,8 @@ __global__ __launch_bounds__(kThreads) void list_copy(const v4u *__restrict__ sr
     if (v < nvec) store16<false>(dst + v, load16<false>(src + v));
 }
 
-// Contiguous streaming copy over tiles of 256*UNROLL vectors (bandwidth probe).
+// Contiguous streaming copy over tiles of 256*UNROLL vectors (bandwidth probe; one
+// vector per lane and one tile per workgroup is what HBM copies fastest).
 template <int UNROLL, bool NTL, bool NTS>
 __global__ __launch_bounds__(kThreads) void probe_copy_kernel(const v4u *__restrict__ src, v4u *__restrict__ dst,
                                                               uint64_t nvec)
@@ -724,39 +725,34 @@ hipError_t launch_list_copy(void *dst, const void *src, uint64_t bytes, hipStrea
     return hipGetLastError();
 }
 
+template <int UNROLL>
+static hipError_t launch_probe(const v4u *sp, v4u *dp, uint64_t nvec, uint32_t grid, uint32_t flags, hipStream_t s)
+{
+    const uint64_t tile = kThreads * UNROLL, tiles = (nvec + tile - 1) / tile;
+    if (grid == 0) grid = UNROLL == 1 ? 1u << 23 : 2048u;
+    const dim3 g(static_cast<uint32_t>(grid < tiles ? grid : tiles)), b(kThreads);
+    const bool ntl = flags & KVP_LAUNCH_NT_LOAD, nts = flags & KVP_LAUNCH_NT_STORE;
+    if (ntl && nts)
+        hipLaunchKernelGGL((probe_copy_kernel<UNROLL, true, true>), g, b, 0, s, sp, dp, nvec);
+    else if (ntl)
+        hipLaunchKernelGGL((probe_copy_kernel<UNROLL, true, false>), g, b, 0, s, sp, dp, nvec);
+    else if (nts)
+        hipLaunchKernelGGL((probe_copy_kernel<UNROLL, false, true>), g, b, 0, s, sp, dp, nvec);
+    else
+        hipLaunchKernelGGL((probe_copy_kernel<UNROLL, false, false>), g, b, 0, s, sp, dp, nvec);
+    return hipGetLastError();
+}
+
 hipError_t launch_probe_copy(void *dst, const void *src, uint64_t bytes, uint32_t grid, uint32_t flags,
                              hipStream_t s)
 {
     const uint64_t nvec = bytes / 16;
     if (nvec == 0) return hipSuccess;
-    const bool split = flags & KVP_LAUNCH_SPLIT2;
-    const uint64_t tiles = (nvec + kThreads * (split ? 4 : 8) - 1) / (kThreads * (split ? 4 : 8));
-    if (grid == 0) grid = 2048;
-    if (grid > tiles) grid = static_cast<uint32_t>(tiles);
-    const bool ntl = flags & KVP_LAUNCH_NT_LOAD, nts = flags & KVP_LAUNCH_NT_STORE;
     const v4u *sp = static_cast<const v4u *>(src);
     v4u *dp = static_cast<v4u *>(dst);
-    dim3 g(grid), b(kThreads);
-    if (split) {
-        if (ntl && nts)
-            hipLaunchKernelGGL((probe_copy_kernel<4, true, true>), g, b, 0, s, sp, dp, nvec);
-        else if (ntl)
-            hipLaunchKernelGGL((probe_copy_kernel<4, true, false>), g, b, 0, s, sp, dp, nvec);
-        else if (nts)
-            hipLaunchKernelGGL((probe_copy_kernel<4, false, true>), g, b, 0, s, sp, dp, nvec);
-        else
-            hipLaunchKernelGGL((probe_copy_kernel<4, false, false>), g, b, 0, s, sp, dp, nvec);
-        return hipGetLastError();
-    }
-    if (ntl && nts)
-        hipLaunchKernelGGL((probe_copy_kernel<8, true, true>), g, b, 0, s, sp, dp, nvec);
-    else if (ntl)
-        hipLaunchKernelGGL((probe_copy_kernel<8, true, false>), g, b, 0, s, sp, dp, nvec);
-    else if (nts)
-        hipLaunchKernelGGL((probe_copy_kernel<8, false, true>), g, b, 0, s, sp, dp, nvec);
-    else
-        hipLaunchKernelGGL((probe_copy_kernel<8, false, false>), g, b, 0, s, sp, dp, nvec);
-    return hipGetLastError();
+    if (flags & KVP_LAUNCH_TILE) return launch_probe<1>(sp, dp, nvec, grid, flags, s);
+    if (flags & KVP_LAUNCH_SPLIT2) return launch_probe<4>(sp, dp, nvec, grid, flags, s);
+    return launch_probe<8>(sp, dp, nvec, grid, flags, s);
 }
 
 }  // namespace kvp

@@ -80,3 +80,17 @@ def test_store_of_one_slot_into_many_blocks():
         assert torch.equal(got, run.src[:, :, torch.from_numpy(q.src_slots.astype(np.int64)).cuda()])
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("vectors", [1, 255, 256, 257, 1024 * 5 + 3])
+@pytest.mark.parametrize("form", [0, K.LAUNCH_SPLIT2, K.LAUNCH_TILE])
+@pytest.mark.parametrize("hints", [0, K.LAUNCH_NT_LOAD, K.LAUNCH_NT_STORE, K.LAUNCH_NT_LOAD | K.LAUNCH_NT_STORE])
+def test_probe_copies(vectors, form, hints):
+    """The probe copy in tiles of 8, 4 and 1 vectors per lane: exactly its bytes, in every form."""
+    src = torch.randint(-2**31, 2**31, (vectors * 4 + 8,), dtype=torch.int32, device="cuda")
+    for grid in (0, 1, 3):
+        dst = torch.zeros_like(src)
+        K.probe_copy_kernel(dst.data_ptr(), src.data_ptr(), vectors * 16, grid, form | hints,
+                            torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(dst[:-8], src[:-8]) and not bool(dst[-8:].any())

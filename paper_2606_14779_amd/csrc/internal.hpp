@@ -241,6 +241,10 @@ struct LaunchCfg {
     bool default_grid;   // the library chose the grid (it may then adapt it per call)
 };
 
+// Pinned memory of work lists: a kernel reads what the host writes again for
+// each call, so the GPU must not keep lines of it from one call to the next.
+constexpr unsigned kListMemory = hipHostMallocMapped | hipHostMallocCoherent;
+
 struct Slot {                    // one work-list buffer of the upload ring
     void *host = nullptr;        // pinned
     void *host_dev = nullptr;    // its device address

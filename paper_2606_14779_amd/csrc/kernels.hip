@@ -526,7 +526,7 @@ ScratchDevice &scratch_setup(int device)
     if (!dev || (reinterpret_cast<uintptr_t>(dev) & 255))
         fail(KVP_ERR_HIP, "scratch symbol has no 256-byte aligned device address");
     void *host = nullptr, *host_dev = nullptr;
-    if (hipHostMalloc(&host, kScratchBytes, hipHostMallocDefault) != hipSuccess || !host) {
+    if (hipHostMalloc(&host, kScratchBytes, kListMemory) != hipSuccess || !host) {
         clear_hip_error();
         fail(KVP_ERR_NOMEM, "pinned staging buffer of the static scratch");
     }

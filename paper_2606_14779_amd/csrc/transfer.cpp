@@ -154,7 +154,7 @@ Slot &acquire_slot(Pool &p, size_t bytes)
         free_slot(s);
         const size_t cap = round_up(std::max(bytes, kSlotMin), kSlotMin);
         void *h = nullptr, *d = nullptr;
-        if (hipHostMalloc(&h, cap, hipHostMallocDefault) != hipSuccess || !h) {
+        if (hipHostMalloc(&h, cap, kListMemory) != hipSuccess || !h) {
             clear_hip_error();
             fail(KVP_ERR_NOMEM, "work-list pinned buffer");
         }

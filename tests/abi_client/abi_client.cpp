@@ -47,12 +47,15 @@
 // executable's hipHostMalloc takes the library's references to the runtime's
 // (the build exports it), so a ring resize can be made to fail on any machine.
 static size_t g_fail_pinned_above = 0;
+static unsigned g_pinned = 0, g_pinned_not_coherent = 0;   // allocations so far
 
 extern "C" hipError_t hipHostMalloc(void **ptr, size_t size, unsigned int flags)
 {
     using Fn = hipError_t (*)(void **, size_t, unsigned int);
     static const Fn real = reinterpret_cast<Fn>(dlvsym(RTLD_NEXT, "hipHostMalloc", "hip_4.2"));
     if (g_fail_pinned_above && size > g_fail_pinned_above) return hipErrorOutOfMemory;
+    ++g_pinned;
+    if (!(flags & hipHostMallocCoherent)) ++g_pinned_not_coherent;
     return real ? real(ptr, size, flags) : hipErrorNotInitialized;
 }
 
@@ -151,7 +154,10 @@ int main(int argc, char **argv)
     // the same request through the upload path: work list uploaded ahead of the launch
     for (uint32_t i = 0; i < 2 * L; ++i) HIPTRY(hipMemset(dst[i], 0xA5, layer_bytes));
     TRY(kv_pool_set_launch(pool, KVP_CLASS_HOST, KVP_OP_RETRIEVE, 0, KVP_LAUNCH_UPLOAD));
+    const unsigned pinned = g_pinned, not_coherent = g_pinned_not_coherent;
     TRY(kv_pool_retrieve(pool, map.data(), n, dst_table.data(), slots, k_dst.data(), v_dst.data(), stream));
+    // the list's buffer, which a kernel reads and later calls write again, is coherent
+    if (g_pinned == pinned || g_pinned_not_coherent != not_coherent) ++bad;
     HIPTRY(hipStreamSynchronize(stream));
     if (check()) return 1;
 

@@ -21,6 +21,24 @@ namespace {
 
 constexpr size_t kMaxFlight = 4096;   // calls in flight from which on no event is created
 
+// Beside a capture of another stream the runtime refuses an event query, and
+// ends that capture too, unless the querying thread's capture mode is relaxed.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { check_hip(hipThreadExchangeStreamCaptureMode(&mode), "hipThreadExchangeStreamCaptureMode"); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    RelaxedCapture(const RelaxedCapture &) = delete;
+    RelaxedCapture &operator=(const RelaxedCapture &) = delete;
+};
+
+bool query(hipEvent_t e)
+{
+    const hipError_t q = hipEventQuery(e);
+    if (q != hipSuccess) clear_hip_error();   // "not ready" is the answer, not an error to leave behind
+    if (q != hipErrorNotReady) check_hip(q, "hipEventQuery");
+    return q == hipSuccess;
+}
+
 void land(Pool &p)   // the oldest call is done
 {
     if (p.flight.front().owned) p.idle.push_back(p.flight.front().done);   // room reserved with the event
@@ -73,23 +91,15 @@ void wait_call(const Pool &p, uint64_t call)
 
 bool event_done(hipEvent_t e)
 {
-    // The query itself under the relaxed capture mode: beside a capture of
-    // another stream the runtime otherwise refuses it, and ends that capture too.
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    check_hip(hipThreadExchangeStreamCaptureMode(&mode), "hipThreadExchangeStreamCaptureMode");
-    const hipError_t q = hipEventQuery(e);
-    if (q != hipSuccess) clear_hip_error();   // "not ready" is the answer, not an error to leave behind
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (q != hipErrorNotReady) check_hip(q, "hipEventQuery");
-    return q == hipSuccess;
+    const RelaxedCapture scope;
+    return query(e);
 }
 
 void land_done_calls(Pool &p)
 {
-    while (!p.flight.empty() && hipPeekAtLastError() == hipSuccess) {
-        if (p.flight.front().done && !event_done(p.flight.front().done)) break;
-        land(p);
-    }
+    if (p.flight.empty() || hipPeekAtLastError() != hipSuccess) return;
+    const RelaxedCapture scope;
+    while (!p.flight.empty() && (!p.flight.front().done || query(p.flight.front().done))) land(p);
 }
 
 hipEvent_t begin_call(Pool &p, hipStream_t s, hipEvent_t lent, hipEvent_t own, bool may_create)

@@ -350,14 +350,19 @@ __device__ __forceinline__ void class_body(const CopyArgs &a)
 // chunk, unit: with work items in slot order it writes up to 64-slot runs of
 // four engine buffers while it reads 4-chunk pieces of each block), the store
 // item by item (it writes whole pool blocks).  Within that order each XCD
-// takes runs of 256 workgroups (1 MiB), so that a page is translated and a
-// DRAM row opened by one die and not by all eight: dealt out one by one, the
-// same order measured 5-15 % less for chunks of 16 KiB and more.  Measured on
-// 8.6 GB in 32 KiB chunks with ascending slots, traffic of the kernel alone:
-// retrieve 6465 GB/s against 5694 for half-chunk units of four vectors per
-// lane in chunk order (5240 for this order without the runs); store 6151
-// against 5407.  Chunks that are no whole number of units (6400 bytes)
-// retrieve at 6122 chunk by chunk and at 5770 in groups of four.
+// takes runs of 256 workgroups (1 MiB) instead of every eighth workgroup.  Whole
+// calls, dealt out one by one / in runs: 8192 LLaMA-shaped blocks over four
+// regions 5843 / 5482 us, 2048 of them token-major 1537 / 1427, the same layer
+// by layer 1691 / 1667, 3271 Qwen3-shaped ones 1721 / 1690, 4096 of those stored
+// and 8192 GPT-OSS-shaped ones level.  What a run gains depends on where the
+// memory lies: blocks of a single region of 4 to 17 GB took -1 to +7 % more time
+// with runs in a retrieve and -5 to +2 % in a store.  It is not translation
+// (level UTCL1 misses in the retrieve, 3 to 50 times as many in the store).
+// Measured on 8.6 GB in 32 KiB chunks with ascending slots, traffic of the kernel
+// alone: retrieve 6465 GB/s against 5694 for half-chunk units of four vectors
+// per lane in chunk order; store 6151 against 5407.  Chunks that are no whole
+// number of units (6400 bytes) retrieve at 6122 chunk by chunk and at 5770 in
+// groups of four.
 //
 // Token-major chunks take the same body: a lane's source vector is looked up
 // by its destination index, so stores stay contiguous and loads come in rows

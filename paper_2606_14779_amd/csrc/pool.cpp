@@ -375,12 +375,15 @@ uint32_t default_flags(uint32_t cls, uint32_t op, const kvp_kv_spec &spec)
     // copy one vector per lane (6407 GB/s of traffic against 6254 with neither
     // hint at 256 threads, 6137 against 5805 at 1024)
     // -- except the loads of token-major pools whose rows are no whole number of
-    // 64 bytes: the units of a chunk then share lines, which a non-temporal load
-    // does not keep for the next (HBM traffic of 4096 blocks, loads non-temporal /
-    // not: rows of 80 bytes retrieve 4964-5190 / 5366-5480 GB/s and store
-    // 5442-5603 / 5518-5595, rows of 160 bytes 5420-5532 / 5467-5534 and
-    // 5581-5681 / 5725-5769; of 64 bytes 5387-5539 / 5525-5591 and 5879-5954 /
-    // 5756-5766; of 256 bytes 6247-6294 / 6078-6109 and 6200-6261 / 6189-6218)
+    // 64 bytes: neighbouring rows then share lines, which a non-temporal load does
+    // not keep in the L1.  With rows of 80 bytes a retrieve asks the L2 for 1.53
+    // times as many lines that way, a store for 1.35 times; HBM reads hardly differ
+    // (2.3 against 0.6 % above the blocks' bytes), and rows of 256 bytes ask for the
+    // same either way.  HBM traffic of 4096 blocks, loads non-temporal / not: rows of
+    // 80 bytes retrieve 4964-5190 / 5366-5480 GB/s and store 5442-5603 / 5518-5595,
+    // of 160 bytes 5420-5532 / 5467-5534 and 5581-5681 / 5725-5769, of 64 bytes
+    // 5387-5539 / 5525-5591 and 5879-5954 / 5756-5766, of 256 bytes 6247-6294 /
+    // 6078-6109 and 6200-6261 / 6189-6218.
     if (cls == KVP_CLASS_STAGING) {
         f |= KVP_LAUNCH_NT_STORE;
         if (spec.pool_layout == 0 || static_cast<uint64_t>(spec.head_dim) * spec.elem_bytes % 64 == 0)

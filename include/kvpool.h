@@ -464,7 +464,7 @@ int kv_pool_set_bandwidths(kvp_pool *pool, const uint64_t *bandwidths);
  * pool has not finished (one that holds the link) takes 48 workgroups: with
  * traffic both ways the
  * link's reads need more in flight (measured on MI355X, a 128K-token
- * LLaMA-shaped store and retrieve at once: 264.6 instead of 320 ms), while
+ * LLaMA-shaped store and retrieve started together: 264.6 instead of 320 ms), while
  * alone, or beside HBM-bound kernels, 12 do as well or better.  An explicit
  * grid is always used as given.
  *

@@ -34,9 +34,11 @@ constexpr size_t kSlotMin = 64 * 1024;   // smallest work-list buffer
 constexpr uint64_t kForkMinBytes = 32ull << 20;
 // Host-class retrieve workgroups while a host-class store of this pool is in
 // flight.  Under two-way traffic the reads need more in flight: a 128K-token
-// LLaMA-shaped store and retrieve at once took 264.6 ms with 48 against
-// 320 ms with the 12 that a lone retrieve wants (which, beside HBM-bound
-// work, loses with more).
+// LLaMA-shaped store and retrieve started together took 264.6 ms with 48
+// against 320 ms with the 12 that a lone retrieve wants (which, beside HBM-bound
+// work, loses with more).  Started 100 ms apart the link serves the later one
+// first with any of them (store / retrieve, the store first: 328 / 220 ms with 48,
+// 277 / 233 with 12).
 constexpr uint32_t kDuplexReadGrid = 48;
 constexpr uint64_t kMergeLdsMax = 20 * 1024;   // 160 KiB of LDS hold 8 workgroups of this size
 constexpr uint64_t kHbmPerLink = 54;           // bytes that HBM moves while the link moves one

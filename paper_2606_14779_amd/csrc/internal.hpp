@@ -272,11 +272,11 @@ struct TimedCall {                // one store / retrieve recorded while timing 
 // `host` is a pinned buffer of the same size, allocated once with it, in
 // which the host writes a call's list before the upload.  Calls take the two
 // halves in turn (a list larger than a half takes both), so that one call's
-// list is written while the previous call still reads its own; `free[h]` is
-// complete when the kernels of the last call that used half h are, and serves
-// as that call's completion event too.
-// Nothing here is ever released: each GPU keeps them until the process ends,
-// and no destructor makes a HIP call at exit.
+// list is written while the previous call still reads its own; `user[h]` is the
+// completion event of the last call that used half h, an event of that call's
+// pool (null: it is known to be done).
+// The memory is never released: each GPU keeps it until the process ends, and
+// no destructor makes a HIP call at exit.
 constexpr uint64_t kScratchBytes = 1ull << 20;
 
 struct ScratchDevice {
@@ -285,13 +285,12 @@ struct ScratchDevice {
     void *dev = nullptr;
     void *host = nullptr;
     void *host_dev = nullptr;   // its device address
-    hipEvent_t free[2] = {nullptr, nullptr};
-    bool free_rec[2] = {false, false};
+    hipEvent_t user[2] = {nullptr, nullptr};
     uint32_t next = 0;          // half of the next call
 };
 
 // Set up the scratch of `device` (the current device) on first use: the
-// array's address by hipGetSymbolAddress, the pinned buffer and the events.
+// array's address by hipGetSymbolAddress and the pinned buffer.
 // Thread safe.  Throws HIP / NOMEM.
 ScratchDevice &scratch_setup(int device);
 // The scratch of a device whose set-up is done (INVALID otherwise); allocates nothing.
@@ -365,6 +364,7 @@ struct Pool {
     uint64_t flight_first = 1;
     std::vector<hipEvent_t> idle;       // events for later calls, with room for every one of the pool
     size_t events = 0;                  // made so far: idle, of calls in flight, of requests
+    hipEvent_t scratch_done[2] = {nullptr, nullptr};   // of allocation-free calls that used a half of the scratch
     // host link, per direction [op]: the last call that holds it, or the record of
     // that call's host-class part; the next one (any stream) waits for it, so calls
     // take the link in turn

@@ -539,21 +539,9 @@ ScratchDevice &scratch_setup(int device)
         (void)hipHostFree(host);
         check_hip(r, "hipHostGetDevicePointer");
     }
-    hipEvent_t ev[2] = {nullptr, nullptr};
-    for (auto &e : ev) {
-        const hipError_t r = hipEventCreateWithFlags(&e, hipEventDisableTiming);
-        if (r != hipSuccess) {
-            for (auto &x : ev)
-                if (x) (void)hipEventDestroy(x);
-            (void)hipHostFree(host);
-            check_hip(r, "hipEventCreate");
-        }
-    }
     sd.dev = dev;
     sd.host = host;
     sd.host_dev = host_dev;
-    sd.free[0] = ev[0];
-    sd.free[1] = ev[1];
     sd.ready = true;
     return sd;
 }

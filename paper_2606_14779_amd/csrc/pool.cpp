@@ -295,8 +295,14 @@ void release_gpu(Pool &p)
     for (auto &r : p.regions) close_file_region(r);
     if (p.s_stage) (void)hipStreamSynchronize(p.s_stage);
     drain_calls(p);
+    if (p.scratch_done[0]) {   // its calls are done: no other pool need wait for them
+        ScratchDevice &sd = scratch_device(p.device);
+        std::lock_guard<std::mutex> lock(sd.mu);
+        for (hipEvent_t &u : sd.user)
+            if (u && (u == p.scratch_done[0] || u == p.scratch_done[1])) u = nullptr;
+    }
     for (auto &s : p.ring) free_slot(s);
-    hipEvent_t *evs[] = {&p.fork, &p.stage_done};
+    hipEvent_t *evs[] = {&p.fork, &p.stage_done, &p.scratch_done[0], &p.scratch_done[1]};
     for (auto e : evs)
         if (*e) (void)hipEventDestroy(*e), *e = nullptr;
     for (auto &tc : p.timed)
@@ -472,6 +478,7 @@ Pool *pool_create(const kvp_region_desc *regions, const uint64_t *bandwidths, ui
         p->ring.resize(kRingSlots);
         for (size_t i = 0; i < kIdleEvents; ++i) add_idle_event(*p);
         (void)scratch_setup(hip_device);   // once per device: the static work-list scratch
+        for (auto &e : p->scratch_done) check_hip(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
         if (!bandwidths) {
             // Eq. 1 from measured bandwidths: each region's read rate into HBM
             std::vector<uint64_t> mbps(n_regions);

@@ -652,11 +652,14 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
         // last call that used it (from any pool, on any stream)
         half = whole ? 0 : sd->next;
         for (uint32_t h = 0; h < 2; ++h) {
-            if (!(whole || h == half) || !sd->free_rec[h]) continue;
-            check_hip(hipEventSynchronize(sd->free[h]), "hipEventSynchronize");
-            forget_event(p, sd->free[h]);   // its next use is another call's
+            const hipEvent_t user = whole || h == half ? sd->user[h] : nullptr;
+            if (!user) continue;
+            check_hip(hipEventSynchronize(user), "hipEventSynchronize");
+            for (hipEvent_t &u : sd->user)
+                if (u == user) u = nullptr;
         }
-        lent = sd->free[half];
+        lent = p.scratch_done[half];   // this pool's earlier calls in this half were over before that one
+        forget_event(p, lent);
         host_list = static_cast<char *>(sd->host) + half * (kScratchBytes / 2);
         host_list_dev = static_cast<char *>(sd->host_dev) + half * (kScratchBytes / 2);
         dev_base = static_cast<char *>(sd->dev) + half * (kScratchBytes / 2);
@@ -675,17 +678,11 @@ void pool_transfer(Pool &p, const kvp_loc *map, uint32_t n_blocks, const int32_t
     begin(holds_link && (fork_staging || !file_batches.empty()));
     check_hip(launch_list_copy(dev_base, host_list_dev, bytes, s), "kernel launch");
     slot = buffer;   // from here on the buffer is in use even if a launch fails
-    auto took_scratch = [&] {   // after finish, which used free[half]
+    auto took_scratch = [&] {   // after finish
         if (!noalloc) return;
-        sd->free_rec[half] = true;
+        sd->user[half] = lent;
+        if (whole) sd->user[1] = lent;
         sd->next = half ^ 1u;
-        if (whole) {
-            if (hipEventRecord(sd->free[1], s) != hipSuccess) {
-                clear_hip_error();
-                (void)hipStreamSynchronize(s);
-            }
-            sd->free_rec[1] = true;
-        }
     };
     // After a failure once the work list is on its way (a file read or write
     // that fails, a launch or copy the runtime refuses), whatever was enqueued

@@ -6,6 +6,8 @@ allocation-free call lives in a static device array shared by every call on
 the GPU, so the checks run calls back to back, the second one smaller, and
 on two streams at once.
 """
+import time
+
 import numpy as np
 import pytest
 
@@ -141,6 +143,50 @@ def test_noalloc_lists_share_the_array():
             assert torch.equal(d[:, at], src[p][:, of]), "call of %d blocks differs" % count
             d[:, at] = 0
             assert not bool(d.any()), "call of %d blocks wrote elsewhere" % count
+    finally:
+        torch.cuda.synchronize()
+        for p in pools:
+            p.close()
+
+
+def test_release_does_not_wait_for_another_pools_call():
+    """A pool's allocation-free calls are done; another pool's, in the same halves of the shared array, wait
+    on a stream that copies hold up.  The first pool releases its request at once, is closed, and the other's
+    calls still land."""
+    spec = K.KVSpec(1, 1, 8, 1, 2, 0)
+    n = 1000
+    table = np.arange(n, dtype=np.int32)
+    say("case noalloc release beside another pool")
+    pools = [K.KVPool([K.Region("staging", n * 32 + 4096)], [1], spec, 0) for _ in range(2)]
+    held = torch.empty(1 << 30, dtype=torch.uint8, pin_memory=True)
+    sink = torch.empty(1 << 30, dtype=torch.uint8, device="cuda")
+    src = torch.randint(-32768, 32767, (2, n, 8), dtype=torch.int16, device="cuda")
+    dst = torch.zeros_like(src)
+    cur, side = torch.cuda.current_stream(), torch.cuda.Stream()
+    try:
+        maps = [p.place(1, n) for p in pools]
+        for p, m in zip(pools, maps):
+            p.store(m, table, n, [src[0].data_ptr()], [src[1].data_ptr()], cur.cuda_stream)
+        for _ in range(2):   # both halves
+            pools[0].retrieve_noalloc(maps[0], table, n, [dst[0].data_ptr()], [dst[1].data_ptr()], cur.cuda_stream)
+        torch.cuda.synchronize()
+        dst.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for _ in range(3):   # about 19 ms each
+                sink.copy_(held, non_blocking=True)
+        for half in (0, 1):
+            part = slice(half * (n // 2), (half + 1) * (n // 2))
+            pools[1].retrieve_noalloc(maps[1][part], table[part], n, [dst[0].data_ptr()], [dst[1].data_ptr()],
+                                      side.cuda_stream)
+        t0 = time.perf_counter()
+        pools[0].release(1)
+        took = time.perf_counter() - t0
+        held_up = not side.query()
+        assert took < 10e-3 and held_up, "released after %.1f ms" % (took * 1e3)
+        pools[0].close()
+        torch.cuda.synchronize()
+        assert torch.equal(dst, src)
     finally:
         torch.cuda.synchronize()
         for p in pools:
